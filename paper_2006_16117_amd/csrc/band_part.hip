@@ -564,7 +564,7 @@ simm_status merge_inverse(const SpikeFactor& f, int* info, hipStream_t st) {
     int *vks = nullptr, *plists = nullptr;
     if (w > kLdsMaxW) {
         const size_t mats = sizeof(cplx) * (size_t)nb * wp * wp;
-        SIMM_HIP_TRY(device_malloc(&gj.q, mats + 2 * sizeof(int) * (size_t)nb * wp));
+        SIMM_HIP_TRY(device_malloc_ordered(&gj.q, mats + 2 * sizeof(int) * (size_t)nb * wp, st));
         Ms = reinterpret_cast<cplx*>(gj.q);
         vks = reinterpret_cast<int*>(static_cast<char*>(gj.q) + mats);
         plists = vks + nb * wp;
@@ -596,7 +596,7 @@ simm_status merge_inverse(const SpikeFactor& f, int* info, hipStream_t st) {
     // pairs, and the products of the last level (nr^2)
     void* mem = nullptr;
     const size_t pz = (size_t)nr * w, ss = (size_t)(nb / 2 + 1) * w * w;
-    SIMM_HIP_TRY(device_malloc(&mem, sizeof(cplx) * (2 * pz + ss + (size_t)nr * nr)));
+    SIMM_HIP_TRY(device_malloc_ordered(&mem, sizeof(cplx) * (2 * pz + ss + (size_t)nr * nr), st));
     fr.q = mem;
     cplx* Pt = reinterpret_cast<cplx*>(mem);
     cplx* Zt = Pt + pz;
@@ -875,7 +875,7 @@ simm_status part_prepare(SpikeFactor& f, hipStream_t st) {
     SIMM_TRY(spikes(f, st));
     stamp("spikes", tp);
     int* info = nullptr;
-    SIMM_HIP_TRY(device_malloc((void**)&info, sizeof(int)));
+    SIMM_HIP_TRY(device_malloc_ordered((void**)&info, sizeof(int), st));
     struct FreeInfo {
         void* q;
         hipStream_t st;

@@ -1257,7 +1257,7 @@ simm_status spike_prepare(SpikeFactor& f, hipStream_t st) {
     if (f.n16 > f.n) hipLaunchKernelGGL(k_pad_ipiv, dim3(1), dim3(16), 0, st, f.n, f.n16, f.ipiv);
     // effective upper bandwidth of U: ku plus the largest interchange distance
     int* d_jump = nullptr;
-    SIMM_HIP_TRY(device_malloc((void**)&d_jump, sizeof(int)));
+    SIMM_HIP_TRY(device_malloc_ordered((void**)&d_jump, sizeof(int), st));
     hipLaunchKernelGGL(k_max_jump, dim3(1), dim3(256), 0, st, f.n, (const int*)f.ipiv, d_jump);
     int jump = 0;
     SIMM_HIP_TRY(hipMemcpyAsync(&jump, d_jump, sizeof(int), hipMemcpyDeviceToHost, st));
@@ -1419,7 +1419,7 @@ simm_status spike_clone_scratch(const SpikeFactor& base, SpikeFactor& out, hipSt
         return (size_t)(p - p0);
     };
     const size_t bytes = layout(nullptr);
-    SIMM_HIP_TRY(device_malloc(&out.mem, bytes));
+    SIMM_HIP_TRY(device_malloc_ordered(&out.mem, bytes, st));
     layout(reinterpret_cast<char*>(out.mem));
     hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, reinterpret_cast<unsigned*>(out.err), 1, 0u);
     hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(256), 0, st, out.counter, (int)((base.G + 1) * SPIKE_CTR_STRIDE), 0u);

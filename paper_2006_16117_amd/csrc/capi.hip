@@ -41,12 +41,28 @@ void clear_error() { g_err.clear(); }
 // RunInFlight.)  Kept blocks are at most an eighth of the device's memory, none while less
 // than a quarter of it is free, and all of them are given back when the last pencil and
 // shift are gone or an allocation fails.
+//
+// Batches (simm_run_batch) keep nothing: their threads (BatchThread) allocate from and free to
+// the runtime, scratch in the order of its stream, and make and destroy their streams.  A
+// batch of 64 pencils aborted on the host twice while its blocks and streams went through
+// the cache and the idle list below; the cause was not found, so batches are off both.
 namespace {
+thread_local bool t_batch = false;
+struct BatchThread {
+    bool old;
+    explicit BatchThread(bool on = true) : old(t_batch) { t_batch = on; }
+    ~BatchThread() { t_batch = old; }
+    BatchThread(const BatchThread&) = delete;
+    BatchThread& operator=(const BatchThread&) = delete;
+};
+
 struct BlockCache {
+    enum Kind { CACHED, PLAIN, ORDERED };   // the cache's; hipMalloc's; hipMallocAsync's
     struct Size {
         int dev;
         size_t bytes;
         bool kept;
+        Kind kind;
     };
     std::mutex mu;
     std::multimap<std::pair<int, size_t>, void*> kept;   // by device and size
@@ -96,12 +112,6 @@ void give_back_blocks() {
     for (void* q : v) (void)hipFree(q);
 }
 
-size_t kept_bytes() {
-    BlockCache& c = cache();
-    std::lock_guard<std::mutex> lk(c.mu);
-    return c.bytes;
-}
-
 // Whether `size` more bytes may be kept on the current device.
 bool may_keep(size_t size) {
     size_t free_b = 0, total_b = 0;
@@ -127,7 +137,8 @@ BlockCache::Size block_of(void* q) {
     BlockCache& c = cache();
     std::lock_guard<std::mutex> lk(c.mu);
     auto it = c.size_of.find(q);
-    return it != c.size_of.end() && !it->second.kept ? it->second : BlockCache::Size{0, 0, false};
+    return it != c.size_of.end() && !it->second.kept ? it->second
+                                                     : BlockCache::Size{0, 0, false, BlockCache::CACHED};
 }
 
 void defer_free(void* q, size_t bytes);
@@ -161,7 +172,7 @@ void retire(const std::vector<void*>& v) {
         const BlockCache::Size z = block_of(q);
         if (z.bytes == 0) continue;
         DeviceGuard dg(z.dev);
-        if (g_runs.load() > 0) {
+        if (z.kind != BlockCache::CACHED || g_runs.load() > 0) {
             {
                 BlockCache& c = cache();
                 std::lock_guard<std::mutex> lk(c.mu);
@@ -179,16 +190,14 @@ void retire(const std::vector<void*>& v) {
 }
 
 // Streams of runs and their worker threads, non-blocking, kept for reuse while a pencil or
-// shift is alive: while one thread destroyed a stream, waits and queries of other threads
-// that meet it (a device-wide free, an event recorded there) worked on objects of the
-// runtime that were already gone; batches make thousands.
+// shift is alive (a batch's threads make and destroy theirs, BatchThread).
 std::mutex g_streams_mu;
 std::vector<std::pair<int, hipStream_t>> g_streams;   // idle, by device
 hipError_t acquire_stream(hipStream_t* st) {
     int dev = 0;
     const hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
-    {
+    if (!t_batch) {
         std::lock_guard<std::mutex> lk(g_streams_mu);
         for (size_t i = 0; i < g_streams.size(); ++i)
             if (g_streams[i].first == dev) {   // the oldest: the order in which calls make theirs stays
@@ -199,9 +208,14 @@ hipError_t acquire_stream(hipStream_t* st) {
     }
     return hipStreamCreateWithFlags(st, hipStreamNonBlocking);
 }
-// st: nothing queued, no thread uses it any more
+// st: no thread uses it any more; a batch's thread returns what a batch's thread acquired
 void return_stream(hipStream_t st) {
     hipDevice_t dev = 0;
+    if (t_batch) {
+        (void)hipStreamSynchronize(st);
+        (void)hipStreamDestroy(st);
+        return;
+    }
     if (hipStreamSynchronize(st) != hipSuccess || hipStreamGetDevice(st, &dev) != hipSuccess) {
         (void)hipGetLastError();
         (void)hipStreamDestroy(st);
@@ -290,9 +304,9 @@ hipError_t device_malloc(void** p, size_t bytes) {
     int dev = 0;
     const hipError_t ed = hipGetDevice(&dev);
     if (ed != hipSuccess) return ed;
-    const std::pair<int, size_t> key{dev, block_size(bytes)};
+    const std::pair<int, size_t> key{dev, t_batch ? std::max<size_t>(bytes, 1) : block_size(bytes)};
     BlockCache& c = cache();
-    {
+    if (!t_batch) {
         std::lock_guard<std::mutex> lk(c.mu);
         auto it = c.kept.find(key);
         if (it != c.kept.end()) {
@@ -312,14 +326,46 @@ hipError_t device_malloc(void** p, size_t bytes) {
     }
     if (e == hipSuccess) {
         std::lock_guard<std::mutex> lk(c.mu);
-        c.size_of[*p] = BlockCache::Size{key.first, key.second, false};
+        c.size_of[*p] = BlockCache::Size{key.first, key.second, false, t_batch ? BlockCache::PLAIN : BlockCache::CACHED};
     }
     return e;
 }
 
-// Frees a block that only work on st has used: waits for st, not for the device.
+// A block that only work on st will use, to be freed with device_free_ordered on st.
+hipError_t device_malloc_ordered(void** p, size_t bytes, hipStream_t st) {
+    if (!t_batch) return device_malloc(p, bytes);
+    int dev = 0;
+    const hipError_t ed = hipGetDevice(&dev);
+    if (ed != hipSuccess) return ed;
+    bytes = std::max<size_t>(bytes, 1);
+    hipError_t e = hipMallocAsync(p, bytes, st);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        flush_deferred_frees();
+        give_back_blocks();
+        e = hipMallocAsync(p, bytes, st);
+    }
+    if (e == hipSuccess) {
+        BlockCache& c = cache();
+        std::lock_guard<std::mutex> lk(c.mu);
+        c.size_of[*p] = BlockCache::Size{dev, bytes, false, BlockCache::ORDERED};
+    }
+    return e;
+}
+
+// Frees a block that only work on st has used: in st's order (a batch's), or after a wait for
+// st, not for the device.
 void device_free_ordered(void* q, hipStream_t st) {
     if (!q) return;
+    if (block_of(q).kind == BlockCache::ORDERED) {
+        BlockCache& c = cache();
+        {
+            std::lock_guard<std::mutex> lk(c.mu);
+            c.size_of.erase(q);
+        }
+        (void)hipFreeAsync(q, st);
+        return;
+    }
     if (hipStreamSynchronize(st) != hipSuccess) {
         (void)hipGetLastError();
         retire({q});
@@ -328,7 +374,8 @@ void device_free_ordered(void* q, hipStream_t st) {
     const BlockCache::Size z = block_of(q);
     if (z.bytes == 0) return;
     DeviceGuard dg(z.dev);
-    keep_or_free(q, z);
+    if (z.kind == BlockCache::CACHED) keep_or_free(q, z);
+    else release_device(q);
 }
 
 // most row blocks of the Gram-Schmidt passes: two workgroups of eight wavefronts a compute
@@ -338,12 +385,7 @@ constexpr int64_t kGsRowBlocks = 512;
 // Alive while a call has worker threads with streams of their own.  Declared after the call's
 // DeferFrees, so that the frees collected are done once the threads are gone.
 struct RunInFlight {
-    // make_room (a batch, of many sizes): blocks that earlier calls left would take the room of
-    // the call's own, whose frees would then be collected and done 16 GB at a time
-    explicit RunInFlight(bool make_room = false) {
-        if (make_room && g_runs.load() == 0 && kept_bytes() > kDeferBytes) give_back_blocks();
-        g_runs.fetch_add(1);
-    }
+    RunInFlight() { g_runs.fetch_add(1); }
     ~RunInFlight() { g_runs.fetch_sub(1); }
     RunInFlight(const RunInFlight&) = delete;
     RunInFlight& operator=(const RunInFlight&) = delete;
@@ -679,7 +721,7 @@ simm_status dalloc(T** p, size_t count) {
 
 // Scratch device buffer of the work on one stream; freeing it waits for that stream (a
 // plain free would wait for the whole device and serialise concurrent runs on other
-// streams).  So it must not outlive the stream: every live buffer is registered with its
+// streams), or comes after its work (a batch's).  So it must not outlive the stream: every live buffer is registered with its
 // stream, and a stream's owner frees what is still registered on it before destroying the
 // stream (release_stream_buffers); the buffer's own destructor then has nothing left to free.
 struct DevBuf;
@@ -715,7 +757,7 @@ struct DevBuf {
     simm_status alloc(size_t bytes, hipStream_t stream) {
         release();
         st = stream;
-        hipError_t e = device_malloc(&p, bytes);
+        hipError_t e = device_malloc_ordered(&p, bytes, st);
         if (e != hipSuccess) {
             p = nullptr;
             set_error(std::string("hipMalloc: ") + hipGetErrorString(e));
@@ -742,6 +784,25 @@ void release_stream_buffers(hipStream_t st) {
         }
         device_free_ordered(q, st);
     }
+}
+
+// The current device's stream-ordered memory pool (a batch's scratch) reuses a block freed on
+// one stream for another stream only once the free has run on the device (not on the
+// strength of event dependencies between the streams: those the runs make are for ordering
+// work, and the pool would otherwise hand a later allocation a block whose free is still
+// pending).  Set once per device.
+std::mutex g_pool_mu;
+std::set<int> g_pool_configured;
+void configure_pool() {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return;
+    std::lock_guard<std::mutex> lk(g_pool_mu);
+    if (!g_pool_configured.insert(dev).second) return;
+    hipMemPool_t pool = nullptr;
+    if (hipDeviceGetDefaultMemPool(&pool, dev) != hipSuccess || !pool) return;
+    int off = 0;
+    (void)hipMemPoolSetAttribute(pool, hipMemPoolReuseFollowEventDependencies, &off);
+    (void)hipMemPoolSetAttribute(pool, hipMemPoolReuseAllowInternalDependencies, &off);
 }
 
 simm_status check_device() {
@@ -1441,6 +1502,7 @@ struct AheadBuild {
     int km = 0;
     hipEvent_t kready = nullptr;
     int dev = 0;
+    bool batch = t_batch;   // the maker's
     simm_pencil_s* pen = nullptr;
     cplx sigma{0, 0};
     int precision = SIMM_PREC_FP64;
@@ -1462,6 +1524,7 @@ struct AheadBuild {
     }
     void thread_main() {
         (void)hipSetDevice(dev);
+        BatchThread bt(batch);
         for (;;) {
             int ph;
             {
@@ -3969,12 +4032,16 @@ simm_status simm_run_batch(const simm_pencil* pencils, const simm_params* params
     SIMM_TRY(check_device());
     int dev = 0;
     SIMM_HIP_TRY(hipGetDevice(&dev));
+    configure_pool();
+    BatchThread batch;
+    give_back_blocks();   // (the batch's memory is not the cache's)
     std::vector<BatchItem> items((size_t)count);
     // steps 1-3 of every pencil: runs in flight on streams of their own, each building its
     // shifts one at a time unless asked for more (the runs in flight share the queues)
     std::atomic<int32_t> next{0};
     auto work = [&]() {
         (void)hipSetDevice(dev);
+        BatchThread bt;
         hipStream_t st = nullptr;
         const hipError_t se = acquire_stream(&st);
         for (;;) {
@@ -4020,7 +4087,7 @@ simm_status simm_run_batch(const simm_pencil* pencils, const simm_params* params
         }
     };
     DeferFrees defer(true);
-    RunInFlight flying(true);
+    RunInFlight flying;
     {
         std::vector<std::thread> pool;
         const int32_t nw = std::min(workers, count);

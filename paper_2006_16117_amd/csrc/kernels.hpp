@@ -11,6 +11,7 @@ namespace simm {
 // Device memory: a block kept for reuse or a new one (any stream may use it at once); frees
 // that wait for the device, and for the one stream whose work used the block.
 hipError_t device_malloc(void** p, size_t bytes);
+hipError_t device_malloc_ordered(void** p, size_t bytes, hipStream_t st);   // for work on st alone
 void release_device(void* p);
 void device_free_ordered(void* p, hipStream_t st);
 

@@ -201,7 +201,7 @@ simm_status solve_backward_error(const SpikeFactor& f, const RefinePencil& pen, 
     const int64_t n = f.n;
     const int64_t n16 = (n + 15) / 16 * 16;
     void* mem = nullptr;
-    SIMM_HIP_TRY(device_malloc(&mem, sizeof(cplx) * 3 * (size_t)n16 + 256));
+    SIMM_HIP_TRY(device_malloc_ordered(&mem, sizeof(cplx) * 3 * (size_t)n16 + 256, st));
     struct Free {
         void* q;
         hipStream_t st;
