@@ -35,7 +35,7 @@ typedef enum {
     SIMM_OK = 0,
     SIMM_EINVAL = -1,           /* bad argument (NaN/Inf input, m < 1, m > n, cap too small, ...) */
     SIMM_ENODEV = -2,           /* no usable gfx950 device */
-    SIMM_ENOMEM = -3,           /* device allocation failed */
+    SIMM_ENOMEM = -3,           /* device (or host) allocation failed */
     SIMM_EHIP = -4,             /* a HIP runtime call failed (message has hipGetErrorString) */
     SIMM_ESINGULAR_SHIFT = -5,  /* exact zero pivot: the shift is an eigenvalue of the pencil */
     SIMM_ENOCONV = -6,          /* the QR iteration for the Schur form of H_m did not converge */

@@ -13,6 +13,7 @@
 #include <atomic>
 #include <chrono>
 #include <functional>
+#include <list>
 #include <unordered_map>
 #include <string>
 #include <thread>
@@ -26,15 +27,65 @@
 namespace simm {
 
 static thread_local std::string g_err;
-void set_error(const std::string& msg) { g_err = msg; }
+void set_error(const std::string& msg) {
+    try {
+        g_err = msg;
+    } catch (...) {   // no memory for the message
+        g_err.clear();
+    }
+}
 void clear_error() { g_err.clear(); }
+
+// The status of the exception being handled.  No C++ exception leaves the library: every
+// entry point ends in SIMM_CATCH, every thread in one of its own.
+static simm_status exception_status() {
+    try {
+        throw;
+    } catch (const std::bad_alloc&) {
+        set_error("host memory");
+        return SIMM_ENOMEM;
+    } catch (const std::exception& e) {
+        g_err.clear();
+        try {
+            g_err = e.what();
+        } catch (...) {
+        }
+        return SIMM_EHIP;
+    } catch (...) {
+        g_err.clear();
+        return SIMM_EHIP;
+    }
+}
+#define SIMM_CATCH \
+    catch (...) {  \
+        return exception_status(); \
+    }
+
+// Starts f on a thread; false if there is none to be had.
+template <typename F>
+static bool start_thread(std::thread& t, F f) {
+    try {
+        t = std::thread(std::move(f));
+        return true;
+    } catch (const std::exception&) {
+        return false;
+    }
+}
+// Joins on every way out of a scope.
+struct JoinThreads {
+    std::vector<std::thread>& v;
+    ~JoinThreads() {
+        for (auto& t : v)
+            if (t.joinable()) t.join();
+    }
+};
 
 // Device blocks are kept for reuse while a pencil or shift is alive.  hipMalloc has to wait
 // for memory freed earlier to be wiped once a process has gone through the device's memory:
 // a run over a 200 x 200 grid (16 factors of 2 GB) took 460 ms and now and then 600 to
-// 3,600 ms, all of it in hipMalloc and hipMallocAsync; now 431 ms every time (six runs over
-// small bands at once 512 -> 288 ms, one application at n = 2,163 with its scratch 67 ->
-// 49 us).  A block enters after a device-wide wait (release_device; hipFree waits as well) or
+// 3,600 ms, all of it in hipMalloc and hipMallocAsync; now 431 ms every time (one application
+// at n = 2,163 with its scratch 67 -> 49 us).  A block enters after a device-wide wait
+// (release_device; hipFree waits as well) or
 // a wait for the stream whose work used it (device_free_ordered), so any stream may take it.
 // (No events: they would be queried after their streams, which runs make and destroy, are
 // gone; and no device-wide wait for want of room while a run's threads are at work,
@@ -46,6 +97,9 @@ void clear_error() { g_err.clear(); }
 // the runtime, scratch in the order of its stream, and make and destroy their streams.  A
 // batch of 64 pencils aborted on the host twice while its blocks and streams went through
 // the cache and the idle list below; the cause was not found, so batches are off both.
+//
+// Frees run in destructors: a block's entry is made when it is allocated and moves between the
+// lists by splicing, so that no free allocates host memory or throws.
 namespace {
 thread_local bool t_batch = false;
 struct BatchThread {
@@ -56,19 +110,27 @@ struct BatchThread {
     BatchThread& operator=(const BatchThread&) = delete;
 };
 
-struct BlockCache {
+struct Block;
+using BlockList = std::list<Block>;
+struct SizeClass {
+    BlockList kept;
+};
+struct Block {
     enum Kind { CACHED, PLAIN, ORDERED };   // the cache's; hipMalloc's; hipMallocAsync's
-    struct Size {
-        int dev;
-        size_t bytes;
-        bool kept;
-        Kind kind;
-    };
+    void* p;
+    int dev;
+    size_t bytes;
+    Kind kind;
+    SizeClass* cls;   // of a cached one
+};
+struct BlockCache {
     std::mutex mu;
-    std::multimap<std::pair<int, size_t>, void*> kept;   // by device and size
-    std::unordered_map<void*, Size> size_of;             // blocks handed out and kept
-    size_t bytes = 0;                                    // of the blocks kept
-    int live = 0;                                        // pencils and shifts
+    std::map<std::pair<int, size_t>, SizeClass> classes;      // by device and size
+    BlockList out;                                            // handed out
+    std::unordered_map<void*, BlockList::iterator> find;      // of those
+    BlockList waiting;                                        // to be freed (DeferFrees)
+    size_t bytes = 0, waiting_bytes = 0;                      // of the blocks kept and waiting
+    int live = 0;                                             // pencils and shifts
 };
 // (never destroyed: objects may outlive the library's own static data)
 BlockCache& cache() {
@@ -94,22 +156,20 @@ struct DeviceGuard {
     }
 };
 
-std::atomic<int> g_runs{0};   // RunInFlight objects
+std::atomic<int> g_runs{0};      // RunInFlight objects
+std::atomic<int> g_batches{0};   // DeferFrees objects
+constexpr size_t kDeferBytes = (size_t)16 << 30;
 
 // Takes all kept blocks out and frees them (each hipFree waits for its device).
 void give_back_blocks() {
-    std::vector<void*> v;
+    BlockList v;
     {
         BlockCache& c = cache();
         std::lock_guard<std::mutex> lk(c.mu);
-        for (auto& kv : c.kept) {
-            v.push_back(kv.second);
-            c.size_of.erase(kv.second);
-        }
-        c.kept.clear();
+        for (auto& kv : c.classes) v.splice(v.end(), kv.second.kept);
         c.bytes = 0;
     }
-    for (void* q : v) (void)hipFree(q);
+    for (Block& b : v) (void)hipFree(b.p);
 }
 
 // Whether `size` more bytes may be kept on the current device.
@@ -132,67 +192,60 @@ bool may_keep(size_t size) {
     return c.live > 0 && c.bytes + size <= limit.load();
 }
 
-// Device and size of a block in use, (.., 0) for memory that is not the cache's.
-BlockCache::Size block_of(void* q) {
+// The block at q, taken from those handed out (into v, empty if it is not one of them).
+void take_block(void* q, BlockList& v) {
     BlockCache& c = cache();
     std::lock_guard<std::mutex> lk(c.mu);
-    auto it = c.size_of.find(q);
-    return it != c.size_of.end() && !it->second.kept ? it->second
-                                                     : BlockCache::Size{0, 0, false, BlockCache::CACHED};
+    const auto it = c.find.find(q);
+    if (it == c.find.end()) return;
+    v.splice(v.end(), c.out, it->second);
+    c.find.erase(it);
 }
 
-void defer_free(void* q, size_t bytes);
+void defer_free(BlockList& v);
 
-// A block nothing on the device uses any more: kept, or freed (a free waits for the whole
+// One block nothing on the device uses any more: kept, or freed (a free waits for the whole
 // device: with the others collected while runs are in flight).
-void keep_or_free(void* q, const BlockCache::Size& z) {
-    BlockCache& c = cache();
-    const bool keep = may_keep(z.bytes), flying = g_runs.load() > 0;
-    {
+void keep_or_free(BlockList& v) {
+    Block& b = v.front();
+    if (may_keep(b.bytes)) {
+        BlockCache& c = cache();
         std::lock_guard<std::mutex> lk(c.mu);
-        auto it = c.size_of.find(q);
-        if (it == c.size_of.end() || it->second.kept) return;
-        if (keep) {
-            it->second.kept = true;
-            c.kept.emplace(std::make_pair(z.dev, z.bytes), q);
-            c.bytes += z.bytes;
-            return;
-        }
-        if (!flying) c.size_of.erase(it);
+        c.bytes += b.bytes;
+        b.cls->kept.splice(b.cls->kept.end(), v);
+    } else if (g_runs.load() > 0) {
+        defer_free(v);
+    } else {
+        (void)hipFree(b.p);
     }
-    if (flying) defer_free(q, z.bytes);
-    else (void)hipFree(q);
 }
 
-// Blocks that work on any stream may still use: one wait per device.  While a run's worker
-// threads make and destroy streams of their own they are freed outright instead.
-void retire(const std::vector<void*>& v) {
-    std::set<int> waited;
-    for (void* q : v) {
-        const BlockCache::Size z = block_of(q);
-        if (z.bytes == 0) continue;
-        DeviceGuard dg(z.dev);
-        if (z.kind != BlockCache::CACHED || g_runs.load() > 0) {
-            {
-                BlockCache& c = cache();
-                std::lock_guard<std::mutex> lk(c.mu);
-                c.size_of.erase(q);
-            }
-            (void)hipFree(q);
+// Blocks that work on any stream may still use: one wait per device.  The cache's own are
+// freed outright, like the others, while a call has worker threads.
+void retire(BlockList& v) {
+    int waited = -1;
+    while (!v.empty()) {
+        BlockList one;
+        one.splice(one.end(), v, v.begin());
+        const Block& b = one.front();
+        DeviceGuard dg(b.dev);
+        if (b.kind != Block::CACHED || g_runs.load() > 0) {
+            (void)hipFree(b.p);
             continue;
         }
-        if (!waited.count(z.dev)) {
+        if (waited != b.dev) {
             (void)hipDeviceSynchronize();
-            waited.insert(z.dev);
+            waited = b.dev;
         }
-        keep_or_free(q, z);
+        keep_or_free(one);
     }
 }
 
 // Streams of runs and their worker threads, non-blocking, kept for reuse while a pencil or
 // shift is alive (a batch's threads make and destroy theirs, BatchThread).
 std::mutex g_streams_mu;
-std::vector<std::pair<int, hipStream_t>> g_streams;   // idle, by device
+std::vector<std::pair<int, hipStream_t>> g_streams;   // idle, by device; room for all made
+size_t g_streams_made = 0;
 hipError_t acquire_stream(hipStream_t* st) {
     int dev = 0;
     const hipError_t e = hipGetDevice(&dev);
@@ -205,6 +258,8 @@ hipError_t acquire_stream(hipStream_t* st) {
                 g_streams.erase(g_streams.begin() + (std::ptrdiff_t)i);
                 return hipSuccess;
             }
+        g_streams.reserve(g_streams_made + 1);
+        ++g_streams_made;
     }
     return hipStreamCreateWithFlags(st, hipStreamNonBlocking);
 }
@@ -225,12 +280,10 @@ void return_stream(hipStream_t st) {
     g_streams.emplace_back((int)dev, st);
 }
 void destroy_streams() {
-    std::vector<std::pair<int, hipStream_t>> v;
-    {
-        std::lock_guard<std::mutex> lk(g_streams_mu);
-        v.swap(g_streams);
-    }
-    for (auto& x : v) (void)hipStreamDestroy(x.second);
+    std::lock_guard<std::mutex> lk(g_streams_mu);
+    for (auto& x : g_streams) (void)hipStreamDestroy(x.second);
+    g_streams_made -= g_streams.size();
+    g_streams.clear();
 }
 
 void object_born() {
@@ -247,135 +300,119 @@ void object_gone() {
     give_back_blocks();
     destroy_streams();
 }
-}  // namespace
 
-// Frees of the buffers a run releases at its end (SIMM_FLAG_RELEASE_FACTORS).  A free
-// waits for the whole device, so while a batch has runs in flight on other streams
-// the buffers are collected and freed together once they add up to kDeferBytes (one
-// wait instead of one per buffer), and at the end of the batch.
-static std::mutex g_free_mu;
-static std::vector<void*> g_free_list;
-static size_t g_free_bytes = 0;
-static std::atomic<int> g_batches{0};
-constexpr size_t kDeferBytes = (size_t)16 << 30;
-
+// A free waits for the whole device, so while a run or batch is in flight on other streams
+// the blocks it releases are collected and freed together once they add up to kDeferBytes
+// (one wait instead of one per block), and at its end.
 void flush_deferred_frees() {
-    std::vector<void*> v;
+    BlockList v;
     {
-        std::lock_guard<std::mutex> lk(g_free_mu);
-        v.swap(g_free_list);
-        g_free_bytes = 0;
+        BlockCache& c = cache();
+        std::lock_guard<std::mutex> lk(c.mu);
+        v.swap(c.waiting);
+        c.waiting_bytes = 0;
     }
-    if (!v.empty()) retire(v);
+    retire(v);
 }
-
-namespace {
-void defer_free(void* q, size_t bytes) {
+void defer_free(BlockList& v) {
     bool flush = false;
     {
-        std::lock_guard<std::mutex> lk(g_free_mu);
-        g_free_list.push_back(q);
-        g_free_bytes += bytes;
-        flush = g_free_bytes >= kDeferBytes;
+        BlockCache& c = cache();
+        std::lock_guard<std::mutex> lk(c.mu);
+        for (Block& b : v) c.waiting_bytes += b.bytes;
+        c.waiting.splice(c.waiting.end(), v);
+        flush = c.waiting_bytes >= kDeferBytes;
     }
     if (flush) flush_deferred_frees();
+}
+
+// Hands out a block: a kept one of its size (CACHED), or a new one from `alloc`; when the
+// device is out of memory, the frees collected so far are done, the kept blocks given back
+// and the allocation is tried once more.
+template <typename Alloc>
+hipError_t new_block(void** p, size_t bytes, Block::Kind kind, Alloc alloc) {
+    *p = nullptr;
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    BlockCache& c = cache();
+    BlockList one;   // the entry, made before the memory
+    one.push_back(Block{nullptr, dev, bytes, kind, nullptr});
+    Block& b = one.front();
+    if (kind == Block::CACHED) {
+        std::lock_guard<std::mutex> lk(c.mu);
+        SizeClass& s = c.classes[std::make_pair(dev, bytes)];
+        if (!s.kept.empty()) {
+            const auto it = std::prev(s.kept.end());
+            c.find.emplace(it->p, it);
+            c.out.splice(c.out.end(), s.kept, it);
+            c.bytes -= bytes;
+            *p = it->p;
+            return hipSuccess;
+        }
+        b.cls = &s;
+    }
+    e = alloc(&b.p, bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        flush_deferred_frees();
+        give_back_blocks();
+        e = alloc(&b.p, bytes);
+    }
+    if (e != hipSuccess) return e;
+    void* const q = b.p;
+    try {
+        std::lock_guard<std::mutex> lk(c.mu);
+        c.find.emplace(q, one.begin());
+        c.out.splice(c.out.end(), one);
+    } catch (...) {
+        (void)hipFree(q);
+        throw;
+    }
+    *p = q;
+    return hipSuccess;
 }
 }  // namespace
 
 void release_device(void* q) {
     if (!q) return;
-    if (g_batches.load() == 0) {
-        retire({q});
-        return;
-    }
-    size_t bytes = 0;
-    {
-        BlockCache& c = cache();
-        std::lock_guard<std::mutex> lk(c.mu);
-        auto it = c.size_of.find(q);
-        if (it != c.size_of.end()) bytes = it->second.bytes;
-    }
-    defer_free(q, bytes);
+    BlockList v;
+    take_block(q, v);
+    if (g_batches.load() == 0) retire(v);
+    else defer_free(v);
 }
 
-// A kept block or a new one; when the device is out of memory, the frees collected so far
-// are done, the kept blocks given back and the allocation is tried once more.
 hipError_t device_malloc(void** p, size_t bytes) {
-    int dev = 0;
-    const hipError_t ed = hipGetDevice(&dev);
-    if (ed != hipSuccess) return ed;
-    const std::pair<int, size_t> key{dev, t_batch ? std::max<size_t>(bytes, 1) : block_size(bytes)};
-    BlockCache& c = cache();
-    if (!t_batch) {
-        std::lock_guard<std::mutex> lk(c.mu);
-        auto it = c.kept.find(key);
-        if (it != c.kept.end()) {
-            *p = it->second;
-            c.size_of[*p].kept = false;
-            c.kept.erase(it);
-            c.bytes -= key.second;
-            return hipSuccess;
-        }
-    }
-    hipError_t e = hipMalloc(p, key.second);
-    if (e == hipErrorOutOfMemory) {
-        (void)hipGetLastError();
-        flush_deferred_frees();
-        give_back_blocks();
-        e = hipMalloc(p, key.second);
-    }
-    if (e == hipSuccess) {
-        std::lock_guard<std::mutex> lk(c.mu);
-        c.size_of[*p] = BlockCache::Size{key.first, key.second, false, t_batch ? BlockCache::PLAIN : BlockCache::CACHED};
-    }
-    return e;
+    const auto alloc = [](void** q, size_t b) { return hipMalloc(q, b); };
+    if (t_batch) return new_block(p, std::max<size_t>(bytes, 1), Block::PLAIN, alloc);
+    return new_block(p, block_size(bytes), Block::CACHED, alloc);
 }
 
 // A block that only work on st will use, to be freed with device_free_ordered on st.
 hipError_t device_malloc_ordered(void** p, size_t bytes, hipStream_t st) {
     if (!t_batch) return device_malloc(p, bytes);
-    int dev = 0;
-    const hipError_t ed = hipGetDevice(&dev);
-    if (ed != hipSuccess) return ed;
-    bytes = std::max<size_t>(bytes, 1);
-    hipError_t e = hipMallocAsync(p, bytes, st);
-    if (e == hipErrorOutOfMemory) {
-        (void)hipGetLastError();
-        flush_deferred_frees();
-        give_back_blocks();
-        e = hipMallocAsync(p, bytes, st);
-    }
-    if (e == hipSuccess) {
-        BlockCache& c = cache();
-        std::lock_guard<std::mutex> lk(c.mu);
-        c.size_of[*p] = BlockCache::Size{dev, bytes, false, BlockCache::ORDERED};
-    }
-    return e;
+    return new_block(p, std::max<size_t>(bytes, 1), Block::ORDERED,
+                     [st](void** q, size_t b) { return hipMallocAsync(q, b, st); });
 }
 
 // Frees a block that only work on st has used: in st's order (a batch's), or after a wait for
 // st, not for the device.
 void device_free_ordered(void* q, hipStream_t st) {
     if (!q) return;
-    if (block_of(q).kind == BlockCache::ORDERED) {
-        BlockCache& c = cache();
-        {
-            std::lock_guard<std::mutex> lk(c.mu);
-            c.size_of.erase(q);
-        }
-        (void)hipFreeAsync(q, st);
-        return;
-    }
-    if (hipStreamSynchronize(st) != hipSuccess) {
+    BlockList v;
+    take_block(q, v);
+    if (v.empty()) return;
+    const Block& b = v.front();
+    if (b.kind == Block::ORDERED) {
+        (void)hipFreeAsync(b.p, st);
+    } else if (b.kind == Block::CACHED && hipStreamSynchronize(st) == hipSuccess) {
+        DeviceGuard dg(b.dev);
+        keep_or_free(v);
+    } else {
         (void)hipGetLastError();
-        retire({q});
-        return;
+        if (g_batches.load() == 0) retire(v);
+        else defer_free(v);
     }
-    const BlockCache::Size z = block_of(q);
-    if (z.bytes == 0) return;
-    DeviceGuard dg(z.dev);
-    if (z.kind == BlockCache::CACHED) keep_or_free(q, z);
-    else release_device(q);
 }
 
 // most row blocks of the Gram-Schmidt passes: two workgroups of eight wavefronts a compute
@@ -414,7 +451,11 @@ using namespace simm;
 // ---------------------------------------------------------------------------
 struct simm_pencil_s {
     simm_pencil_s() { object_born(); }
-    ~simm_pencil_s() { object_gone(); }
+    ~simm_pencil_s() {
+        release_device(A);
+        release_device(B);
+        object_gone();
+    }
     simm_pencil_s(const simm_pencil_s&) = delete;
     simm_pencil_s& operator=(const simm_pencil_s&) = delete;
     int64_t n = 0;
@@ -597,10 +638,10 @@ struct KernelClock {
     hipStream_t st = nullptr;
     std::vector<Mark> marks;
     void begin(int k) {
-        hipEvent_t a = nullptr;
+        marks.push_back({k, nullptr, nullptr, 1});
+        hipEvent_t& a = marks.back().a;
         (void)hipEventCreate(&a);
         (void)hipEventRecord(a, st);
-        marks.push_back({k, a, nullptr, 1});
     }
     void end(int64_t units) {
         hipEvent_t b = nullptr;
@@ -1489,7 +1530,6 @@ struct AheadBuild {
     std::mutex mu;
     std::unique_ptr<simm_shift_s> s;
     simm_status rc = SIMM_OK;   // status of the last phase run
-    std::string err;
     KernelClock clock;
     hipStream_t st = nullptr;
     std::atomic<bool> cancel{false};
@@ -1535,11 +1575,15 @@ struct AheadBuild {
                 }
                 ph = done + 1;
             }
-            const simm_status r = run_phase(ph);
+            simm_status r;
+            try {
+                r = run_phase(ph);
+            } catch (...) {
+                r = exception_status();
+            }
             std::lock_guard<std::mutex> lk(mu);
             rc = r;
-            if (r != SIMM_OK) err = g_err;
-            else done = ph;
+            if (r == SIMM_OK) done = ph;
         }
     }
     void start(simm_pencil_s* p, cplx sig, bool timed_, int precision_) {
@@ -1549,12 +1593,19 @@ struct AheadBuild {
         pen = p;
         sigma = sig;
         running = true;
-        th = std::thread([this]() { thread_main(); });
+        spawn();
+    }
+    // without a thread the build counts as failed (the caller then builds one at a time)
+    void spawn() {
+        if (start_thread(th, [this]() { thread_main(); })) return;
+        std::lock_guard<std::mutex> lk(mu);
+        running = false;
+        rc = SIMM_EHIP;
     }
     // asks for phases up to `level` (2: the Krylov phase, start vector f written on
     // the run's stream before `ready`)
     void request(int level, const cplx* f = nullptr, int m = 0, hipEvent_t ready = nullptr) {
-        bool spawn = false;
+        bool again = false;
         {
             std::lock_guard<std::mutex> lk(mu);
             if (level <= want) return;
@@ -1564,11 +1615,11 @@ struct AheadBuild {
                 km = m;
                 kready = ready;
             }
-            if (!running && rc == SIMM_OK) running = spawn = true;
+            if (!running && rc == SIMM_OK) running = again = true;
         }
-        if (spawn) {   // the thread has finished what it was asked for: run the rest on a new one
+        if (again) {   // the thread has finished what it was asked for: run the rest on a new one
             if (th.joinable()) th.join();
-            th = std::thread([this]() { thread_main(); });
+            spawn();
         }
     }
     int wanted() {
@@ -1763,7 +1814,10 @@ simm_status associate(simm_pencil_s* p, const simm_params* prm, const cplx* f_de
         dropped.push_back(std::move(b));
     };
     auto drop_all = [&]() {
-        for (auto& kv : ahead) drop(std::move(kv.second));
+        for (auto& kv : ahead)
+            if (kv.second) kv.second->cancel.store(true);
+        for (auto& kv : ahead)
+            if (kv.second) kv.second->finish(clk ? R->kms : nullptr, clk ? R->kcnt : nullptr);
         ahead.clear();
         release_dropped();
     };
@@ -2867,6 +2921,24 @@ simm_status to_device_vec(const double* src, int32_t mem, int64_t count, DevBuf&
     return SIMM_OK;
 }
 
+// f(w) for w < W, each on a thread of its own and f(0) on this one (f returns by itself and
+// does not throw); those that get no thread run here.
+template <typename F>
+void on_workers(int W, F& f) {
+    std::vector<std::thread> pool;
+    JoinThreads join{pool};
+    std::vector<int> here;
+    pool.reserve((size_t)W);
+    here.reserve((size_t)W);
+    here.push_back(0);
+    for (int w = 1; w < W; ++w) {
+        std::thread t;
+        if (start_thread(t, [&f, w]() { f(w); })) pool.push_back(std::move(t));
+        else here.push_back(w);
+    }
+    for (int w : here) f(w);
+}
+
 // Multiplicities (Sec. 3.4) of the clusters of a finished run: see simm_multiplicities.
 constexpr int MULT_WORKERS = 4;
 
@@ -2971,6 +3043,11 @@ simm_status multiplicities(simm_result_s* R, const cplx* F, int k, double rel_to
                 const int64_t* idxd = offd + q.off.size();
                 SpikeFactor clone{};
                 const bool own = W > 1 || NB > 1;
+                struct Release {
+                    SpikeFactor* c;
+                    hipStream_t st;
+                    ~Release() { spike_release_ordered(*c, st); }
+                } release{&clone, x.st};
                 if (own) SIMM_TRY(spike_clone_scratch(base->spike, clone, x.st, NB));
                 for (int b = w; b < nblocks; b += W) {
                     // Krylov spaces of f_i, i in block b, on the shift's factor
@@ -2999,7 +3076,6 @@ simm_status multiplicities(simm_result_s* R, const cplx* F, int k, double rel_to
                     int e = 0;
                     SIMM_HIP_TRY(hipMemcpyAsync(&e, clone.err, sizeof(int), hipMemcpyDeviceToHost, x.st));
                     SIMM_HIP_TRY(hipStreamSynchronize(x.st));
-                    spike_release_ordered(clone, x.st);
                     if (e) {
                         set_error("partitioned sweep: a chunk-chain barrier timed out");
                         return SIMM_EHIP;
@@ -3009,15 +3085,14 @@ simm_status multiplicities(simm_result_s* R, const cplx* F, int k, double rel_to
             SIMM_HIP_TRY(hipStreamSynchronize(x.st));
             return SIMM_OK;
         };
-        x.rc = body();
-        if (x.rc != SIMM_OK) x.msg = simm_last_error();
+        try {
+            x.rc = body();
+            if (x.rc != SIMM_OK) x.msg = simm_last_error();
+        } catch (...) {
+            x.rc = exception_status();
+        }
     };
-    {
-        std::vector<std::thread> pool;
-        for (int w = 1; w < W; ++w) pool.emplace_back(work, w);
-        work(0);
-        for (auto& t : pool) t.join();
-    }
+    on_workers(W, work);
     for (auto& x : wk)
         if (x.rc != SIMM_OK) {
             set_error(x.msg);
@@ -3091,13 +3166,6 @@ simm_status gradient(const std::vector<simm_shift_s*>& shifts, const std::vector
 
     // the conjugate-transposed pencil
     simm_pencil_s adj;
-    struct AdjRelease {
-        simm_pencil_s* q;
-        ~AdjRelease() {
-            release_device(q->A);
-            release_device(q->B);
-        }
-    } adj_release{&adj};
     adj.n = n;
     adj.kla = p->kua;
     adj.kua = p->kla;
@@ -3279,18 +3347,16 @@ simm_status gradient(const std::vector<simm_shift_s*>& shifts, const std::vector
                 if ((int)((first + q) % W) != w) continue;
                 const int64_t k0 = q * NB;
                 const int nb = (int)std::min<int64_t>(NB, (int64_t)rs.size() - k0);
-                const simm_status rc = block(x, w, rs.data() + k0, nb);
-                if (rc != SIMM_OK) {
-                    x.rc = rc;
-                    x.msg = simm_last_error();
-                    return;
+                try {
+                    x.rc = block(x, w, rs.data() + k0, nb);
+                    if (x.rc != SIMM_OK) x.msg = simm_last_error();
+                } catch (...) {
+                    x.rc = exception_status();
                 }
+                if (x.rc != SIMM_OK) return;
             }
         };
-        std::vector<std::thread> pool;
-        for (int w = 1; w < W; ++w) pool.emplace_back(run_worker, w);
-        run_worker(0);
-        for (auto& t : pool) t.join();
+        on_workers(W, run_worker);
         next_worker = (first + nblocks) % W;
         for (auto& x : wk) {
             if (x.rc != SIMM_OK) {
@@ -3349,7 +3415,7 @@ extern "C" {
 const char* simm_last_error(void) { return g_err.c_str(); }
 int32_t simm_version(void) { return 1; }
 
-simm_status simm_params_default(simm_params* p) {
+simm_status simm_params_default(simm_params* p) try {
     if (!p) return SIMM_EINVAL;
     std::memset(p, 0, sizeof(*p));
     p->x0 = -1;
@@ -3370,10 +3436,11 @@ simm_status simm_params_default(simm_params* p) {
     p->precision = SIMM_PREC_FP64;
     return SIMM_OK;
 }
+SIMM_CATCH
 
 simm_status simm_pencil_create_banded(int64_t n, int32_t kl_a, int32_t ku_a, const double* a_band, int32_t kl_b,
                                       int32_t ku_b, const double* b_band, int32_t mem, void* hip_stream,
-                                      simm_pencil* out) {
+                                      simm_pencil* out) try {
     clear_error();
     if (!out) return SIMM_EINVAL;
     *out = nullptr;
@@ -3412,10 +3479,11 @@ simm_status simm_pencil_create_banded(int64_t n, int32_t kl_a, int32_t ku_a, con
     *out = p.release();
     return SIMM_OK;
 }
+SIMM_CATCH
 
 simm_status simm_pencil_create_csr(int64_t n, const int64_t* a_rowptr, const int32_t* a_col, const double* a_val,
                                    const int64_t* b_rowptr, const int32_t* b_col, const double* b_val,
-                                   void* hip_stream, simm_pencil* out) {
+                                   void* hip_stream, simm_pencil* out) try {
     clear_error();
     if (!out || n < 1 || !a_rowptr || !a_col || !a_val || (b_rowptr && (!b_col || !b_val))) {
         set_error("bad CSR arguments");
@@ -3462,24 +3530,23 @@ simm_status simm_pencil_create_csr(int64_t n, const int64_t* a_rowptr, const int
     return simm_pencil_create_banded(n, kla, kua, ab.data(), klb, kub, b_rowptr ? bb.data() : nullptr,
                                      SIMM_MEM_HOST, hip_stream, out);
 }
+SIMM_CATCH
 
-simm_status simm_pencil_info(simm_pencil p, int64_t* n, int32_t* kl, int32_t* ku) {
+simm_status simm_pencil_info(simm_pencil p, int64_t* n, int32_t* kl, int32_t* ku) try {
     if (!p) return SIMM_EINVAL;
     if (n) *n = p->n;
     if (kl) *kl = std::max(p->kla, p->klb);
     if (ku) *ku = std::max(p->kua, p->kub);
     return SIMM_OK;
 }
+SIMM_CATCH
 
 void simm_pencil_destroy(simm_pencil p) {
-    if (!p) return;
-    release_device(p->A);
-    release_device(p->B);
     delete p;
 }
 
 simm_status simm_shift_build(simm_pencil p, double sig_re, double sig_im, const double* f, int32_t f_mem, int32_t m,
-                             int32_t precision, void* hip_stream, simm_shift* out) {
+                             int32_t precision, void* hip_stream, simm_shift* out) try {
     clear_error();
     if (!out) return SIMM_EINVAL;
     *out = nullptr;
@@ -3508,9 +3575,10 @@ simm_status simm_shift_build(simm_pencil p, double sig_re, double sig_im, const 
     *out = s.release();
     return SIMM_OK;
 }
+SIMM_CATCH
 
 simm_status simm_shift_from_hessenberg(double sig_re, double sig_im, double beta, const double* H, int32_t m_eff,
-                                       void* hip_stream, simm_shift* out) {
+                                       void* hip_stream, simm_shift* out) try {
     clear_error();
     if (!out) return SIMM_EINVAL;
     *out = nullptr;
@@ -3556,8 +3624,9 @@ simm_status simm_shift_from_hessenberg(double sig_re, double sig_im, double beta
     *out = s.release();
     return SIMM_OK;
 }
+SIMM_CATCH
 
-simm_status simm_shift_info(simm_shift s, double* sigma, double* beta, int32_t* m_eff, double* H, double* ritz) {
+simm_status simm_shift_info(simm_shift s, double* sigma, double* beta, int32_t* m_eff, double* H, double* ritz) try {
     if (!s) return SIMM_EINVAL;
     if (sigma) {
         sigma[0] = s->sigma.re;
@@ -3569,8 +3638,9 @@ simm_status simm_shift_info(simm_shift s, double* sigma, double* beta, int32_t* 
     if (ritz) std::memcpy(ritz, s->ritz.data(), sizeof(cplx) * s->ritz.size());
     return SIMM_OK;
 }
+SIMM_CATCH
 
-simm_status simm_shift_basis(simm_shift s, double* V, int32_t mem, void* hip_stream) {
+simm_status simm_shift_basis(simm_shift s, double* V, int32_t mem, void* hip_stream) try {
     clear_error();
     if (!s || !V) return SIMM_EINVAL;
     if (!s->has_factor()) {
@@ -3584,8 +3654,9 @@ simm_status simm_shift_basis(simm_shift s, double* V, int32_t mem, void* hip_str
     SIMM_HIP_TRY(hipStreamSynchronize(st));
     return SIMM_OK;
 }
+SIMM_CATCH
 
-simm_status simm_shift_apply(simm_shift s, const double* x, double* y, int32_t mem, void* hip_stream) {
+simm_status simm_shift_apply(simm_shift s, const double* x, double* y, int32_t mem, void* hip_stream) try {
     clear_error();
     if (!s || !x || !y || x == y) {
         set_error("bad apply arguments");
@@ -3614,9 +3685,10 @@ simm_status simm_shift_apply(simm_shift s, const double* x, double* y, int32_t m
     SIMM_HIP_TRY(hipStreamSynchronize(st));
     return SIMM_OK;
 }
+SIMM_CATCH
 
 simm_status simm_shift_apply_many(simm_shift s, const double* X, double* Y, int32_t k, int32_t mem,
-                                  void* hip_stream) {
+                                  void* hip_stream) try {
     clear_error();
     if (!s || !X || !Y || X == Y || k < 0) {
         set_error("bad apply arguments");
@@ -3683,13 +3755,14 @@ simm_status simm_shift_apply_many(simm_shift s, const double* X, double* Y, int3
     }
     return SIMM_OK;
 }
+SIMM_CATCH
 
 void simm_shift_destroy(simm_shift s) {
     if (s && !s->borrowed) delete s;
 }
 
 simm_status simm_cell_residuals(simm_shift s, int32_t level, const int64_t* squares, int64_t n_squares,
-                                const simm_params* params, double* rho_max, int32_t mem, void* hip_stream) {
+                                const simm_params* params, double* rho_max, int32_t mem, void* hip_stream) try {
     clear_error();
     if (!s || !params || n_squares < 0 || (n_squares > 0 && (!squares || !rho_max)) || level < 1 || level > 60) {
         set_error("bad cell-residual arguments");
@@ -3742,11 +3815,12 @@ simm_status simm_cell_residuals(simm_shift s, int32_t level, const int64_t* squa
     }
     return SIMM_OK;
 }
+SIMM_CATCH
 
 simm_status simm_indicators(const simm_shift* shifts, int32_t n_shifts, const int64_t* regions, int64_t n_regions,
                             const simm_params* params, double* indicator, double* rho_max, double* nsf, double* nsc,
                             double* Tf, uint8_t* decision, double* sums, int32_t m_max, int32_t mem,
-                            void* hip_stream) {
+                            void* hip_stream) try {
     clear_error();
     if (!shifts || n_shifts < 1 || (!regions && n_regions > 0) || n_regions < 0 || !params) {
         set_error("bad indicator arguments");
@@ -3831,10 +3905,11 @@ simm_status simm_indicators(const simm_shift* shifts, int32_t n_shifts, const in
     SIMM_HIP_TRY(hipStreamSynchronize(st));
     return SIMM_OK;
 }
+SIMM_CATCH
 
 simm_status simm_gradient(const simm_shift* shifts, int32_t n_shifts, const int64_t* regions, int64_t n_regions,
                           const simm_params* params, int32_t kl1, int32_t ku1, const double* a1_band, double* J,
-                          double* dJdp, double* grad_diag, int32_t mem, void* hip_stream) {
+                          double* dJdp, double* grad_diag, int32_t mem, void* hip_stream) try {
     clear_error();
     DeferFrees defer(true);
     RunInFlight flying;
@@ -3911,9 +3986,10 @@ simm_status simm_gradient(const simm_shift* shifts, int32_t n_shifts, const int6
     SIMM_HIP_TRY(hipStreamSynchronize(st));
     return SIMM_OK;
 }
+SIMM_CATCH
 
 simm_status simm_project(simm_shift s, const double* Y, int64_t c, double* X, double* col_norms, int32_t precision,
-                         void* hip_stream) {
+                         void* hip_stream) try {
     clear_error();
     if (!s || c < 0 || (c > 0 && (!Y || (!X && !col_norms)))) {
         set_error("bad projection arguments");
@@ -3937,9 +4013,10 @@ simm_status simm_project(simm_shift s, const double* Y, int64_t c, double* X, do
     SIMM_HIP_TRY(hipStreamSynchronize(st));
     return SIMM_OK;
 }
+SIMM_CATCH
 
 simm_status simm_project_noalloc(simm_shift s, const double* Y, int64_t c, double* X, double* col_norms,
-                                 int32_t precision, void* hip_stream) {
+                                 int32_t precision, void* hip_stream) try {
     clear_error();
     if (!s || c < 0 || (c > 0 && (!Y || (!X && !col_norms)))) {
         set_error("bad projection arguments");
@@ -3972,9 +4049,10 @@ simm_status simm_project_noalloc(simm_shift s, const double* Y, int64_t c, doubl
     return project(s->p->n, s->m_eff, s->V, s->p->n, reinterpret_cast<const cplx*>(Y), s->m_eff, c,
                    reinterpret_cast<cplx*>(X), col_norms, scr, se, precision, st);
 }
+SIMM_CATCH
 
 simm_status simm_run(simm_pencil p, const simm_params* params, const double* f, int32_t f_mem, void* hip_stream,
-                     simm_result* out) {
+                     simm_result* out) try {
     clear_error();
     if (!out) return SIMM_EINVAL;
     *out = nullptr;
@@ -3987,32 +4065,25 @@ simm_status simm_run(simm_pencil p, const simm_params* params, const double* f, 
     const cplx* fd = nullptr;
     SIMM_TRY(to_device_vec(f, f_mem, p->n, fb, &fd, st));
     auto R = std::make_unique<simm_result_s>();
-    hipEvent_t e0, e1;
-    SIMM_HIP_TRY(hipEventCreate(&e0));
-    SIMM_HIP_TRY(hipEventCreate(&e1));
-    SIMM_HIP_TRY(hipEventRecord(e0, st));
+    double ms = 0.0;
     simm_status rc;
     {
+        Timer t(st, &ms);
         // frees during the run (factors computed ahead and dropped, factors released
         // per shift) are collected and done together at its end
         DeferFrees defer(true);
         RunInFlight flying;
         rc = run(p, params, fd, st, R.get());
     }
-    (void)hipEventRecord(e1, st);
-    (void)hipEventSynchronize(e1);
-    float ms = 0;
-    (void)hipEventElapsedTime(&ms, e0, e1);
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
     if (rc != SIMM_OK) return rc;
     R->ms[3] = ms;
     *out = R.release();
     return SIMM_OK;
 }
+SIMM_CATCH
 
 simm_status simm_run_batch(const simm_pencil* pencils, const simm_params* params, const double* const* f,
-                           int32_t f_mem, int32_t count, int32_t workers, simm_result* out) {
+                           int32_t f_mem, int32_t count, int32_t workers, simm_result* out) try {
     clear_error();
     if (!pencils || !params || !f || !out || count < 0 || workers < 1) {
         set_error("bad batch arguments");
@@ -4048,37 +4119,41 @@ simm_status simm_run_batch(const simm_pencil* pencils, const simm_params* params
             const int32_t i = next.fetch_add(1);
             if (i >= count) break;
             BatchItem& it = items[(size_t)i];
-            it.p = pencils[i];
-            it.prm = params[i];
-            if (it.prm.lookahead == 0) it.prm.lookahead = 1;
-            it.R = std::make_unique<simm_result_s>();
-            if (se != hipSuccess) {
-                it.rc = SIMM_EHIP;
-                it.msg = std::string("hipStreamCreateWithFlags: ") + hipGetErrorString(se);
-                continue;
+            try {
+                it.p = pencils[i];
+                it.prm = params[i];
+                if (it.prm.lookahead == 0) it.prm.lookahead = 1;
+                it.R = std::make_unique<simm_result_s>();
+                if (se != hipSuccess) {
+                    it.rc = SIMM_EHIP;
+                    it.msg = std::string("hipStreamCreateWithFlags: ") + hipGetErrorString(se);
+                    continue;
+                }
+                auto phase = [&]() -> simm_status {
+                    int nx, ny, K;
+                    SIMM_TRY(validate_params(&it.prm, it.p->n, &nx, &ny, &K));
+                    it.R->K = K;
+                    it.R->prm = it.prm;
+                    it.R->pencil = it.p;
+                    DevBuf fb;
+                    const cplx* fd = nullptr;
+                    SIMM_TRY(to_device_vec(f[i], f_mem, it.p->n, fb, &fd, st));
+                    Rule rule;
+                    SIMM_TRY(rule.make(it.prm.gauss_per_edge, st));
+                    SIMM_TRY(associate(it.p, &it.prm, fd, st, it.R.get(), rule, nullptr, it.cur));
+                    SIMM_HIP_TRY(hipStreamSynchronize(st));
+                    return SIMM_OK;
+                };
+                const auto t0 = std::chrono::steady_clock::now();
+                it.rc = phase();
+                if (it.rc != SIMM_OK) it.msg = simm_last_error();
+                it.R->ms[3] += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
+                if (batch_progress())
+                    std::fprintf(stderr, "[simm batch] pencil %d: n = %lld, %zu shifts, %.0f ms\n", (int)i,
+                                 (long long)it.p->n, it.R->shifts.size(), it.R->ms[3]);
+            } catch (...) {
+                it.rc = exception_status();
             }
-            auto phase = [&]() -> simm_status {
-                int nx, ny, K;
-                SIMM_TRY(validate_params(&it.prm, it.p->n, &nx, &ny, &K));
-                it.R->K = K;
-                it.R->prm = it.prm;
-                it.R->pencil = it.p;
-                DevBuf fb;
-                const cplx* fd = nullptr;
-                SIMM_TRY(to_device_vec(f[i], f_mem, it.p->n, fb, &fd, st));
-                Rule rule;
-                SIMM_TRY(rule.make(it.prm.gauss_per_edge, st));
-                SIMM_TRY(associate(it.p, &it.prm, fd, st, it.R.get(), rule, nullptr, it.cur));
-                SIMM_HIP_TRY(hipStreamSynchronize(st));
-                return SIMM_OK;
-            };
-            const auto t0 = std::chrono::steady_clock::now();
-            it.rc = phase();
-            if (it.rc != SIMM_OK) it.msg = simm_last_error();
-            it.R->ms[3] += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
-            if (batch_progress())
-                std::fprintf(stderr, "[simm batch] pencil %d: n = %lld, %zu shifts, %.0f ms\n", (int)i,
-                             (long long)it.p->n, it.R->shifts.size(), it.R->ms[3]);
         }
         if (se == hipSuccess) {
             release_stream_buffers(st);
@@ -4089,10 +4164,10 @@ simm_status simm_run_batch(const simm_pencil* pencils, const simm_params* params
     DeferFrees defer(true);
     RunInFlight flying;
     {
-        std::vector<std::thread> pool;
+        // (one of them on this thread: with fewer threads than asked for, or none, it goes on)
         const int32_t nw = std::min(workers, count);
-        for (int32_t w = 0; w < nw; ++w) pool.emplace_back(work);
-        for (auto& t : pool) t.join();
+        auto worker = [&](int) { work(); };
+        on_workers(nw, worker);
     }
     auto fail_at = [&](int32_t i, const std::string& m) {
         set_error("pencil " + std::to_string(i) + ": " + m);
@@ -4150,8 +4225,9 @@ simm_status simm_run_batch(const simm_pencil* pencils, const simm_params* params
     for (int32_t i = 0; i < count; ++i) out[i] = items[(size_t)i].R.release();
     return SIMM_OK;
 }
+SIMM_CATCH
 
-simm_status simm_batch_tuning(int64_t* entries, int64_t* trials, int32_t* ind_grid, int32_t* proj_grid, int64_t cap) {
+simm_status simm_batch_tuning(int64_t* entries, int64_t* trials, int32_t* ind_grid, int32_t* proj_grid, int64_t cap) try {
     std::lock_guard<std::mutex> lk(g_tune.mu);
     const int64_t ne = (int64_t)(g_tune.ind.size() + g_tune.proj.size());
     if (entries) *entries = ne;
@@ -4164,9 +4240,10 @@ simm_status simm_batch_tuning(int64_t* entries, int64_t* trials, int32_t* ind_gr
         if (proj_grid && q < cap) proj_grid[q++] = kv.second;
     return SIMM_OK;
 }
+SIMM_CATCH
 
 simm_status simm_result_summary(simm_result r, int32_t* K, int32_t* n_shifts, int64_t* n_clusters,
-                                int64_t* n_unresolved) {
+                                int64_t* n_unresolved) try {
     if (!r) return SIMM_EINVAL;
     if (K) *K = r->K;
     if (n_shifts) *n_shifts = (int32_t)r->shifts.size();
@@ -4179,9 +4256,10 @@ simm_status simm_result_summary(simm_result r, int32_t* K, int32_t* n_shifts, in
     }
     return SIMM_OK;
 }
+SIMM_CATCH
 
 simm_status simm_result_level(simm_result r, int32_t level, int64_t* n_tested, int64_t* ix, int64_t* iy,
-                              int32_t* shift, double* indicator, double* rho_max, uint8_t* decision, int64_t cap) {
+                              int32_t* shift, double* indicator, double* rho_max, uint8_t* decision, int64_t cap) try {
     clear_error();
     if (!r || !n_tested || level < 1 || level > (int32_t)r->levels.size()) {
         set_error("bad level");
@@ -4204,8 +4282,9 @@ simm_status simm_result_level(simm_result r, int32_t level, int64_t* n_tested, i
     }
     return SIMM_OK;
 }
+SIMM_CATCH
 
-simm_status simm_result_full_indicators(simm_result r, int32_t level, double* out, int64_t cap) {
+simm_status simm_result_full_indicators(simm_result r, int32_t level, double* out, int64_t cap) try {
     clear_error();
     if (!r || level < 1 || level > (int32_t)r->levels.size()) {
         set_error("bad level");
@@ -4220,15 +4299,17 @@ simm_status simm_result_full_indicators(simm_result r, int32_t level, double* ou
     for (int64_t q = 0; q < N; ++q) out[q] = L.full_indicator[q];
     return SIMM_OK;
 }
+SIMM_CATCH
 
-simm_status simm_result_shift(simm_result r, int32_t idx, simm_shift* out) {
+simm_status simm_result_shift(simm_result r, int32_t idx, simm_shift* out) try {
     if (!r || !out || idx < 0 || idx >= (int32_t)r->shifts.size()) return SIMM_EINVAL;
     *out = r->shifts[idx].get();
     return SIMM_OK;
 }
+SIMM_CATCH
 
 simm_status simm_result_clusters(simm_result r, int64_t* n, double* lam, double* lam_ritz, int32_t* shift,
-                                 int32_t* flags, int64_t cap) {
+                                 int32_t* flags, int64_t cap) try {
     clear_error();
     if (!r || !n) return SIMM_EINVAL;
     const int64_t N = (int64_t)r->clusters.size();
@@ -4252,9 +4333,10 @@ simm_status simm_result_clusters(simm_result r, int64_t* n, double* lam, double*
     }
     return SIMM_OK;
 }
+SIMM_CATCH
 
 simm_status simm_multiplicities(simm_result r, const double* F, int32_t k, int32_t f_mem, double rel_tol,
-                                void* hip_stream, int32_t* mult, double* sv, int64_t cap) {
+                                void* hip_stream, int32_t* mult, double* sv, int64_t cap) try {
     clear_error();
     DeferFrees defer(true);
     RunInFlight flying;
@@ -4281,8 +4363,9 @@ simm_status simm_multiplicities(simm_result r, const double* F, int32_t k, int32
     SIMM_TRY(to_device_vec(F, f_mem, r->pencil->n * (int64_t)k, fb, &fd, st));
     return multiplicities(r, fd, k, rel_tol, st, mult, sv);
 }
+SIMM_CATCH
 
-simm_status simm_result_stats(simm_result r, double* ms4, int64_t* counters3) {
+simm_status simm_result_stats(simm_result r, double* ms4, int64_t* counters3) try {
     if (!r) return SIMM_EINVAL;
     if (ms4)
         for (int i = 0; i < 4; ++i) ms4[i] = r->ms[i];
@@ -4290,9 +4373,10 @@ simm_status simm_result_stats(simm_result r, double* ms4, int64_t* counters3) {
         for (int i = 0; i < 3; ++i) counters3[i] = r->counters[i];
     return SIMM_OK;
 }
+SIMM_CATCH
 
 simm_status simm_result_refine_stats(simm_result r, int64_t* solves, int64_t* corrections, int32_t* fallbacks,
-                                     double* max_eta) {
+                                     double* max_eta) try {
     if (!r) return SIMM_EINVAL;
     if (solves) *solves = r->refine_solves;
     if (corrections) *corrections = r->refine_corrections;
@@ -4300,8 +4384,9 @@ simm_status simm_result_refine_stats(simm_result r, int64_t* solves, int64_t* co
     if (max_eta) *max_eta = r->refine_max_eta;
     return SIMM_OK;
 }
+SIMM_CATCH
 
-simm_status simm_shift_refine_stats(simm_shift s, int64_t* solves, int64_t* corrections, double* max_eta) {
+simm_status simm_shift_refine_stats(simm_shift s, int64_t* solves, int64_t* corrections, double* max_eta) try {
     clear_error();
     if (!s) return SIMM_EINVAL;
     long long stats[2] = {0, 0};
@@ -4317,8 +4402,9 @@ simm_status simm_shift_refine_stats(simm_shift s, int64_t* solves, int64_t* corr
     if (max_eta) *max_eta = eta;
     return SIMM_OK;
 }
+SIMM_CATCH
 
-simm_status simm_shift_factor_info(simm_shift s, int64_t* block_len, int32_t* fallback, double* eta) {
+simm_status simm_shift_factor_info(simm_shift s, int64_t* block_len, int32_t* fallback, double* eta) try {
     clear_error();
     if (!s) return SIMM_EINVAL;
     if (block_len) *block_len = s->part_bs;
@@ -4326,8 +4412,9 @@ simm_status simm_shift_factor_info(simm_shift s, int64_t* block_len, int32_t* fa
     if (eta) *eta = s->part_eta;
     return SIMM_OK;
 }
+SIMM_CATCH
 
-simm_status simm_result_kernel_stats(simm_result r, double* ms, int64_t* launches) {
+simm_status simm_result_kernel_stats(simm_result r, double* ms, int64_t* launches) try {
     if (!r) return SIMM_EINVAL;
     for (int k = 0; k < SIMM_K_COUNT; ++k) {
         if (ms) ms[k] = r->kms[k];
@@ -4335,6 +4422,7 @@ simm_status simm_result_kernel_stats(simm_result r, double* ms, int64_t* launche
     }
     return SIMM_OK;
 }
+SIMM_CATCH
 
 void simm_result_destroy(simm_result r) { delete r; }
 

@@ -15,3 +15,4 @@ struct FakeHip {
     pthread_t main_thread = pthread_self();
 };
 FakeHip& fake_hip();
+extern thread_local int fake_hip_inside;   // calls of the runtime this thread is in

@@ -1,9 +1,16 @@
 // Host logic of the library (memory, streams, threads, errors) on the runtime of
 // fake_hip.cpp: host_cases CASE, exit status 0 if the case holds.
+#include <dlfcn.h>
+#include <errno.h>
+#include <pthread.h>
+
+#include <algorithm>
+#include <atomic>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -18,6 +25,26 @@ static int failed = 0;
             ++failed;                                                                 \
         }                                                                             \
     } while (0)
+
+// The library's allocations: the one numbered fail_at fails (none if negative).
+static std::atomic<long> allocations{0}, fail_at{-1};
+void* operator new(size_t bytes) {
+    if (fake_hip_inside == 0 && allocations.fetch_add(1) == fail_at.load()) throw std::bad_alloc();
+    if (void* p = std::malloc(bytes ? bytes : 1)) return p;
+    throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
+
+// Threads: none to be had once threads_left is 0 (no limit if negative).
+static std::atomic<long> threads_left{-1};
+extern "C" int pthread_create(pthread_t* t, const pthread_attr_t* a, void* (*f)(void*), void* arg) {
+    using Create = int (*)(pthread_t*, const pthread_attr_t*, void* (*)(void*), void*);
+    static Create create = (Create)dlsym(RTLD_NEXT, "pthread_create");
+    if (threads_left.load() == 0) return EAGAIN;
+    if (threads_left.load() > 0) threads_left.fetch_sub(1);
+    return create(t, a, f, arg);
+}
 
 static simm_pencil band(int64_t n, int kl, int ku) {
     std::vector<double> a(2 * (size_t)(kl + ku + 1) * n, 0.5);
@@ -92,9 +119,88 @@ static void batch_keeps_nothing() {
     CHECK(h.used == pencils_only);
 }
 
+static std::vector<double> ones(int64_t count) { return std::vector<double>(2 * (size_t)count, 1.0); }
+
+// A run, its multiplicities and the gradient of one of its squares; the first error.
+static simm_status whole_use(simm_pencil p, const std::vector<double>& f) {
+    const simm_params q = run_params(SIMM_FLAG_PROJECT, 3);
+    simm_result r = nullptr;
+    simm_status rc = simm_run(p, &q, f.data(), SIMM_MEM_HOST, nullptr, &r);
+    if (rc != SIMM_OK) {
+        CHECK(r == nullptr);
+        return rc;
+    }
+    int64_t nc = 0, n = 0;
+    int32_t ns = 0, kl = 0, ku = 0;
+    simm_result_summary(r, nullptr, &ns, &nc, nullptr);
+    simm_pencil_info(p, &n, &kl, &ku);
+    CHECK(ns > 1 && nc > 0);
+    ++fake_hip_inside;   // (not the library's)
+    std::vector<double> F((size_t)(2 * n * 6), 1.0), grad((size_t)(2 * n));
+    std::vector<int32_t> mult((size_t)nc);
+    --fake_hip_inside;
+    rc = simm_multiplicities(r, F.data(), 6, SIMM_MEM_HOST, 1e-6, nullptr, mult.data(), nullptr, nc);
+    simm_shift s = nullptr;
+    if (rc == SIMM_OK) rc = simm_result_shift(r, 0, &s);
+    if (rc == SIMM_OK) {
+        const int64_t squares[] = {1, 1, 1, 0, 1, 2, 1, 0, 1, 1, 2, 0, 1, 2, 2, 0, 2, 3, 3, 0};
+        double J = 0.0;
+        rc = simm_gradient(&s, 1, squares, 5, &q, 0, 0, nullptr, &J, nullptr, grad.data(), SIMM_MEM_HOST, nullptr);
+    }
+    simm_result_destroy(r);
+    return rc;
+}
+
+// Calls do their work where the system gives them no thread, or fewer than they ask for.
+static void no_threads() {
+    for (long left : {0L, 1L, 3L, -1L}) {
+        threads_left = left;
+        simm_pencil p = band(500, 8, 8);
+        const simm_status rc = whole_use(p, ones(500));
+        if (rc != SIMM_OK) std::printf("%ld threads: %s\n", left, simm_last_error());
+        CHECK(rc == SIMM_OK);
+        simm_pencil_destroy(p);
+        Batch b(5, SIMM_FLAG_RELEASE_FACTORS);
+        CHECK(b.run(3) == SIMM_OK);
+    }
+}
+
+// Where host memory runs out a call returns ENOMEM (or a message cut short), keeps no memory of
+// the device and leaves the library fit for the next call.
+static void no_host_memory() {
+    for (int batch = 0; batch < 2; ++batch) {
+        long total = 0, errors = 0;
+        for (long k = -1; k < total; k += std::max<long>(1, total / 300)) {
+            {
+                const std::vector<double> f = ones(500);
+                simm_pencil p = band(500, 8, 8);
+                Batch b(batch ? 4 : 0, SIMM_FLAG_RELEASE_FACTORS | SIMM_FLAG_PROJECT);
+                if (batch) b.out.assign(b.pencils.size(), nullptr);
+                allocations = 0;
+                fail_at = k;
+                const simm_status rc = batch ? simm_run_batch(b.pencils.data(), b.prm.data(), b.fp.data(), SIMM_MEM_HOST,
+                                                              4, 3, b.out.data())
+                                             : whole_use(p, f);
+                fail_at = -1;
+                if (k < 0) {
+                    total = allocations.load();
+                    CHECK(rc == SIMM_OK && total > 100);
+                } else if (rc != SIMM_OK) {
+                    ++errors;
+                }
+                simm_pencil_destroy(p);
+            }
+            CHECK(fake_hip().used == 0);
+        }
+        CHECK(errors > 50);
+    }
+}
+
 int main(int argc, char** argv) {
     const std::map<std::string, void (*)()> cases = {
         {"batch_keeps_nothing", batch_keeps_nothing},
+        {"no_threads", no_threads},
+        {"no_host_memory", no_host_memory},
     };
     const auto it = cases.find(argc > 1 ? argv[1] : "");
     if (it == cases.end()) return 2;
