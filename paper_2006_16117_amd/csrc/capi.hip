@@ -110,6 +110,9 @@ struct BatchThread {
     BatchThread& operator=(const BatchThread&) = delete;
 };
 
+// Threads that a call starts beside its own.
+thread_local bool t_helper = false;
+
 struct Block;
 using BlockList = std::list<Block>;
 struct SizeClass {
@@ -303,7 +306,8 @@ void object_gone() {
 
 // A free waits for the whole device, so while a run or batch is in flight on other streams
 // the blocks it releases are collected and freed together once they add up to kDeferBytes
-// (one wait instead of one per block), and at its end.
+// (one wait instead of one per block), and at its end: by the call's own thread, except in
+// batches, whose threads have no call's work beside them, and where memory ran out (new_block).
 void flush_deferred_frees() {
     BlockList v;
     {
@@ -321,7 +325,7 @@ void defer_free(BlockList& v) {
         std::lock_guard<std::mutex> lk(c.mu);
         for (Block& b : v) c.waiting_bytes += b.bytes;
         c.waiting.splice(c.waiting.end(), v);
-        flush = c.waiting_bytes >= kDeferBytes;
+        flush = c.waiting_bytes >= kDeferBytes && (t_batch || !t_helper);
     }
     if (flush) flush_deferred_frees();
 }
@@ -1565,6 +1569,7 @@ struct AheadBuild {
     void thread_main() {
         (void)hipSetDevice(dev);
         BatchThread bt(batch);
+        t_helper = true;
         for (;;) {
             int ph;
             {
@@ -2933,7 +2938,11 @@ void on_workers(int W, F& f) {
     here.push_back(0);
     for (int w = 1; w < W; ++w) {
         std::thread t;
-        if (start_thread(t, [&f, w]() { f(w); })) pool.push_back(std::move(t));
+        if (start_thread(t, [&f, w]() {
+                t_helper = true;
+                f(w);
+            }))
+            pool.push_back(std::move(t));
         else here.push_back(w);
     }
     for (int w : here) f(w);

@@ -151,6 +151,24 @@ static simm_status whole_use(simm_pencil p, const std::vector<double>& f) {
     return rc;
 }
 
+// The threads a run starts beside its own free nothing to the device (its memory is large
+// enough); what they release is freed by the run's thread.
+static void helpers_free_nothing() {
+    FakeHip& h = fake_hip();
+    const int64_t n = 1 << 20;
+    const std::vector<double> f = ones(n);
+    simm_pencil p = band(n, 8, 8);
+    h.total = (size_t)110 << 30;   // too little is free for blocks to be kept
+    simm_params q = run_params(0, 6);
+    q.n1 = 8;
+    simm_result r = nullptr;
+    CHECK(simm_run(p, &q, f.data(), SIMM_MEM_HOST, nullptr, &r) == SIMM_OK);
+    std::printf("%ld blocks freed, %ld by other threads, %.1f GB at most\n", h.frees, h.frees_elsewhere, h.peak / 1e9);
+    CHECK(h.frees > 0 && h.frees_elsewhere == 0);
+    simm_result_destroy(r);
+    simm_pencil_destroy(p);
+}
+
 // Calls do their work where the system gives them no thread, or fewer than they ask for.
 static void no_threads() {
     for (long left : {0L, 1L, 3L, -1L}) {
@@ -199,6 +217,7 @@ static void no_host_memory() {
 int main(int argc, char** argv) {
     const std::map<std::string, void (*)()> cases = {
         {"batch_keeps_nothing", batch_keeps_nothing},
+        {"helpers_free_nothing", helpers_free_nothing},
         {"no_threads", no_threads},
         {"no_host_memory", no_host_memory},
     };
