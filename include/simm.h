@@ -129,8 +129,9 @@ simm_status simm_pencil_info(simm_pencil p, int64_t* n, int32_t* kl, int32_t* ku
 /* Shifts and results made on a pencil refer to it (applications of M, Krylov
  * spaces for multiplicities): destroy the pencil after them. */
 /* Device memory of shifts and scratch that are gone is kept for later calls while a pencil or
- * shift is alive (at most an eighth of the device's memory, none while less than a quarter
- * of it is free) and given back with the last of them. */
+ * shift is alive: at most an eighth of the device's memory, and at most 64 MB once less than a
+ * quarter of it is free.  It is given back with the last of them, where an allocation fails,
+ * and to a batch (simm_run_batch keeps none). */
 void simm_pencil_destroy(simm_pencil p);
 
 /* ------------------------------------------------------------------------ */

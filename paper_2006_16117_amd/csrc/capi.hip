@@ -89,9 +89,10 @@ struct JoinThreads {
 // a wait for the stream whose work used it (device_free_ordered), so any stream may take it.
 // (No events: they would be queried after their streams, which runs make and destroy, are
 // gone; and no device-wide wait for want of room while a run's threads are at work,
-// RunInFlight.)  Kept blocks are at most an eighth of the device's memory, none while less
-// than a quarter of it is free, and all of them are given back when the last pencil and
-// shift are gone or an allocation fails.
+// RunInFlight.)  Kept blocks are at most an eighth of the device's memory; the sizes not
+// asked for the longest make room for others.  What is free is looked at for every block of
+// 64 MB and whenever 64 MB have been kept since: less than a quarter, and all kept blocks are
+// given back, as they are when the last pencil and shift are gone or an allocation fails.
 //
 // Batches (simm_run_batch) keep nothing: their threads (BatchThread) allocate from and free to
 // the runtime, scratch in the order of its stream, and make and destroy their streams.  A
@@ -117,6 +118,7 @@ struct Block;
 using BlockList = std::list<Block>;
 struct SizeClass {
     BlockList kept;
+    uint64_t asked = 0;   // BlockCache::clock at the last request of this size
 };
 struct Block {
     enum Kind { CACHED, PLAIN, ORDERED };   // the cache's; hipMalloc's; hipMallocAsync's
@@ -133,6 +135,8 @@ struct BlockCache {
     std::unordered_map<void*, BlockList::iterator> find;      // of those
     BlockList waiting;                                        // to be freed (DeferFrees)
     size_t bytes = 0, waiting_bytes = 0;                      // of the blocks kept and waiting
+    size_t unchecked = 0;                                     // kept since free memory was looked at
+    uint64_t clock = 0;                                       // requests
     int live = 0;                                             // pencils and shifts
 };
 // (never destroyed: objects may outlive the library's own static data)
@@ -170,29 +174,54 @@ void give_back_blocks() {
         BlockCache& c = cache();
         std::lock_guard<std::mutex> lk(c.mu);
         for (auto& kv : c.classes) v.splice(v.end(), kv.second.kept);
-        c.bytes = 0;
+        c.bytes = c.unchecked = 0;
     }
     for (Block& b : v) (void)hipFree(b.p);
 }
 
-// Whether `size` more bytes may be kept on the current device.
-bool may_keep(size_t size) {
+// Whether `size` more bytes may be kept on the current device.  Kept blocks of the sizes that
+// were not asked for the longest go where that makes room (into `evicted`, to be freed; not
+// while runs are in flight).
+bool may_keep(int dev, size_t size, BlockList& evicted) {
+    BlockCache& c = cache();
+    const bool flying = g_runs.load() > 0;
+    bool look;
+    {
+        std::lock_guard<std::mutex> lk(c.mu);
+        if (c.live == 0) return false;
+        look = c.unchecked + size >= ((size_t)64 << 20);
+    }
     size_t free_b = 0, total_b = 0;
-    if (size >= ((size_t)64 << 20)) {
+    if (look) {
         if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return false;
         if (free_b < total_b / 4) {
-            if (g_runs.load() == 0) give_back_blocks();
+            if (!flying) give_back_blocks();
             return false;
         }
     }
-    static std::atomic<size_t> limit{0};
-    if (limit.load() == 0) {
-        if (total_b == 0 && hipMemGetInfo(&free_b, &total_b) != hipSuccess) return false;
-        limit.store(total_b / 8);
-    }
-    BlockCache& c = cache();
+    static std::map<int, size_t> limits;   // (under c.mu) by device
     std::lock_guard<std::mutex> lk(c.mu);
-    return c.live > 0 && c.bytes + size <= limit.load();
+    const auto it = limits.find(dev);
+    size_t limit = it != limits.end() ? it->second : 0;
+    if (limit == 0) {
+        if (total_b == 0 && hipMemGetInfo(&free_b, &total_b) != hipSuccess) return false;
+        limit = total_b / 8;
+        try {
+            limits[dev] = limit;
+        } catch (...) {   // (asked for again the next time)
+        }
+    }
+    if (look) c.unchecked = 0;
+    if (size > limit) return false;
+    while (c.bytes + size > limit && !flying) {
+        SizeClass* old = nullptr;
+        for (auto& kv : c.classes)
+            if (!kv.second.kept.empty() && (!old || kv.second.asked < old->asked)) old = &kv.second;
+        if (!old) break;
+        c.bytes -= old->kept.front().bytes;
+        evicted.splice(evicted.end(), old->kept, old->kept.begin());
+    }
+    return c.bytes + size <= limit;
 }
 
 // The block at q, taken from those handed out (into v, empty if it is not one of them).
@@ -206,21 +235,25 @@ void take_block(void* q, BlockList& v) {
 }
 
 void defer_free(BlockList& v);
+void flush_deferred_frees();
 
 // One block nothing on the device uses any more: kept, or freed (a free waits for the whole
 // device: with the others collected while runs are in flight).
 void keep_or_free(BlockList& v) {
     Block& b = v.front();
-    if (may_keep(b.bytes)) {
+    BlockList evicted;
+    if (may_keep(b.dev, b.bytes, evicted)) {
         BlockCache& c = cache();
         std::lock_guard<std::mutex> lk(c.mu);
         c.bytes += b.bytes;
+        c.unchecked += b.bytes;
         b.cls->kept.splice(b.cls->kept.end(), v);
     } else if (g_runs.load() > 0) {
         defer_free(v);
     } else {
         (void)hipFree(b.p);
     }
+    for (Block& e : evicted) (void)hipFree(e.p);
 }
 
 // Blocks that work on any stream may still use: one wait per device.  The cache's own are
@@ -300,6 +333,7 @@ void object_gone() {
         std::lock_guard<std::mutex> lk(c.mu);
         if (--c.live > 0) return;
     }
+    flush_deferred_frees();   // (those of other threads' calls)
     give_back_blocks();
     destroy_streams();
 }
@@ -327,6 +361,7 @@ void defer_free(BlockList& v) {
         c.waiting.splice(c.waiting.end(), v);
         flush = c.waiting_bytes >= kDeferBytes && (t_batch || !t_helper);
     }
+    flush |= g_batches.load() == 0;   // the last DeferFrees ended meanwhile
     if (flush) flush_deferred_frees();
 }
 
@@ -346,6 +381,7 @@ hipError_t new_block(void** p, size_t bytes, Block::Kind kind, Alloc alloc) {
     if (kind == Block::CACHED) {
         std::lock_guard<std::mutex> lk(c.mu);
         SizeClass& s = c.classes[std::make_pair(dev, bytes)];
+        s.asked = ++c.clock;
         if (!s.kept.empty()) {
             const auto it = std::prev(s.kept.end());
             c.find.emplace(it->p, it);

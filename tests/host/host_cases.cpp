@@ -151,6 +151,53 @@ static simm_status whole_use(simm_pencil p, const std::vector<double>& f) {
     return rc;
 }
 
+extern "C" int hipMalloc(void** p, size_t bytes);
+extern "C" int hipFree(void* p);
+
+// Builds and destroys a shift of order n and half-bandwidth 8.
+static void build_one(int64_t n) {
+    const std::vector<double> f = ones(n);
+    simm_pencil p = band(n, 8, 8);
+    simm_shift s = nullptr;
+    CHECK(simm_shift_build(p, 0.1, 0.2, f.data(), SIMM_MEM_HOST, 8, SIMM_PREC_FP64, nullptr, &s) == SIMM_OK);
+    simm_shift_destroy(s);
+    simm_pencil_destroy(p);
+}
+
+// Small blocks too are kept only while a quarter of the memory is free.
+static void kept_while_a_quarter_is_free() {
+    FakeHip& h = fake_hip();
+    h.total = (size_t)4 << 30;
+    void* ballast = nullptr;
+    CHECK(hipMalloc(&ballast, (size_t)3328 << 20) == 0);
+    simm_pencil held = band(300, 8, 8);
+    const size_t base = h.used;
+    size_t most = 0;
+    for (int64_t n = 2000; n < 22000; n += 400) {
+        build_one(n);
+        most = std::max(most, h.used - base);
+    }
+    std::printf("%.0f MB kept\n", most / 1e6);
+    CHECK(most <= ((size_t)64 << 20));
+    simm_pencil_destroy(held);
+    hipFree(ballast);
+}
+
+// Blocks of sizes that are not asked for any more make room for those that are.
+static void sizes_in_use_are_kept() {
+    FakeHip& h = fake_hip();
+    h.total = (size_t)4 << 30;   // 512 MB of blocks at most
+    simm_pencil held = band(300, 8, 8);
+    for (int64_t n = 2000; n < 40000; n += 800) build_one(n);
+    CHECK(h.used <= ((size_t)513 << 20));
+    for (int i = 0; i < 3; ++i) build_one(60000);
+    const long before = h.mallocs;
+    for (int i = 0; i < 3; ++i) build_one(60000);
+    std::printf("%ld allocations in three builds\n", h.mallocs - before);
+    CHECK(h.mallocs == before);
+    simm_pencil_destroy(held);
+}
+
 // The threads a run starts beside its own free nothing to the device (its memory is large
 // enough); what they release is freed by the run's thread.
 static void helpers_free_nothing() {
@@ -217,6 +264,8 @@ static void no_host_memory() {
 int main(int argc, char** argv) {
     const std::map<std::string, void (*)()> cases = {
         {"batch_keeps_nothing", batch_keeps_nothing},
+        {"kept_while_a_quarter_is_free", kept_while_a_quarter_is_free},
+        {"sizes_in_use_are_kept", sizes_in_use_are_kept},
         {"helpers_free_nothing", helpers_free_nothing},
         {"no_threads", no_threads},
         {"no_host_memory", no_host_memory},
