@@ -835,6 +835,13 @@ simm_status part_cut(int64_t n, int kl, int ku, cplxf* AB, int64_t bs, cplx* cpl
     return cut_t(n, kl, ku, AB, bs, cpl, st);
 }
 
+size_t part_prepare_bytes(int64_t n, int kl, int ku, int64_t bs, size_t spike_scratch) {
+    const size_t n16 = (size_t)((n + 15) / 16 * 16), w = (size_t)(kl + ku), nb = (size_t)((n + bs - 1) / bs) - 1;
+    const size_t nr = nb * w;
+    const size_t merge = sizeof(cplx) * (2 * nr * w + (nb / 2 + 1) * w * w + nr * nr);
+    return sizeof(cplx) * (n16 * w + nr * nr + n16 + nr) + std::max(spike_scratch, merge);
+}
+
 simm_status part_prepare(SpikeFactor& f, hipStream_t st) {
     const int kl = f.kl, ku = f.ku, w = kl + ku;
     f.pkl = kl;

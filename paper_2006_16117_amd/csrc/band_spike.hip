@@ -1252,28 +1252,8 @@ static simm_status prepare_blocks(SpikeFactor& f, const GT* LP, const GT* AB, GT
     return SIMM_OK;
 }
 
-simm_status spike_prepare(SpikeFactor& f, hipStream_t st) {
-    f.n16 = (f.n + 15) / 16 * 16;
-    if (f.n16 > f.n) hipLaunchKernelGGL(k_pad_ipiv, dim3(1), dim3(16), 0, st, f.n, f.n16, f.ipiv);
-    // effective upper bandwidth of U: ku plus the largest interchange distance
-    int* d_jump = nullptr;
-    SIMM_HIP_TRY(device_malloc_ordered((void**)&d_jump, sizeof(int), st));
-    hipLaunchKernelGGL(k_max_jump, dim3(1), dim3(256), 0, st, f.n, (const int*)f.ipiv, d_jump);
-    int jump = 0;
-    SIMM_HIP_TRY(hipMemcpyAsync(&jump, d_jump, sizeof(int), hipMemcpyDeviceToHost, st));
-    SIMM_HIP_TRY(hipStreamSynchronize(st));
-    device_free_ordered(d_jump, st);
-    f.K = (int)std::min<int64_t>(std::min<int64_t>(f.kl + f.ku, f.ku + std::max(0, jump)), f.n - 1);
-    f.K = std::max(f.K, 1);
-    f.klx = std::max(1, (int)std::min<int64_t>(f.kl, f.n - 1));
-    if (f.n > (int64_t)1 << 30) {
-        set_error("order above 2^30 is not supported by the partitioned sweeps");
-        return SIMM_EUNSUPPORTED;
-    }
-    if (f.klx + 16 > 1024 || f.K + 16 > 1024) {
-        set_error("band too wide for the partitioned sweeps (bandwidth + 16 > 1024)");
-        return SIMM_EUNSUPPORTED;
-    }
+// Chunks, groups and blocks of the sweeps of a factor (order, bandwidths and block length given).
+static void sweep_layout(SpikeFactor& f) {
     f.cbs = 0;
     if (f.bs > 0) {
         f.nbk = (f.n + f.bs - 1) / f.bs;
@@ -1301,23 +1281,62 @@ simm_status spike_prepare(SpikeFactor& f, hipStream_t st) {
         f.L = (f.P + G - 1) / G;
         f.G = (f.P + f.L - 1) / f.L;
     }
-    f.Wf = chunk_threads(f.klx + 16);
-    f.Wb = chunk_threads(f.K + 16);
+}
+
+// Device memory of the sweep data: responses only where chunks have states (psi), products of
+// 2 .. cpb - 2 transfer matrices inside a block (inner).
+struct SweepSizes {
+    size_t psi, inner, perms, bytes;
+};
+static SweepSizes sweep_sizes(const SpikeFactor& f) {
     const int kl = f.klx, K = f.K;
     const int64_t n16 = f.n16;
+    SweepSizes z{};
     const size_t two = f.G > 1 ? 1 : 0;    // transfer products only with more than one group
-    const size_t psi = (f.cbs > 0 && f.cpb == 1) ? 0 : 1;   // responses only where chunks have states
-    // products of 2 .. cpb - 2 transfer matrices inside a block
-    const size_t inner = (f.cbs > 0 && f.cpb > 3) ? (size_t)(f.cpb - 3) * (size_t)(f.cpb - 2) * (size_t)f.nbk : 0;
+    z.psi = (f.cbs > 0 && f.cpb == 1) ? 0 : 1;
+    z.inner = (f.cbs > 0 && f.cpb > 3) ? (size_t)(f.cpb - 3) * (size_t)(f.cpb - 2) * (size_t)f.nbk : 0;
     // n-sized per-panel blocks and unit-state responses, in the factor's precision
-    const size_t big = (size_t)n16 * (kl + 16) + (size_t)n16 * (K + 16) + psi * ((size_t)n16 * kl + (size_t)n16 * K);
+    const size_t big = (size_t)n16 * (kl + 16) + (size_t)n16 * (K + 16) + z.psi * ((size_t)n16 * kl + (size_t)n16 * K);
     const size_t esz = f.f32 ? sizeof(cplxf) : sizeof(cplx);
     const size_t elems = (size_t)f.P * kl * kl + (size_t)f.P * K * K + (size_t)f.P * kl * 2 + (size_t)f.P * K * 2 +
                          (size_t)n16 + two * ((size_t)(f.P + f.G) * ((size_t)kl * kl + (size_t)K * K)) +
                          (size_t)f.G * 2 * (kl + K) + (size_t)(f.G + 1) * 16 + 64 +
-                         inner * ((size_t)kl * kl + (size_t)K * K);
-    const size_t perms = (size_t)(n16 / 16) * (kl + 16);
-    SIMM_HIP_TRY(device_malloc(&f.mem, sizeof(cplx) * elems + esz * big + sizeof(uint16_t) * perms + 25 * 256));
+                         z.inner * ((size_t)kl * kl + (size_t)K * K);
+    z.perms = (size_t)(n16 / 16) * (kl + 16);
+    z.bytes = sizeof(cplx) * elems + esz * big + sizeof(uint16_t) * z.perms + 25 * 256;
+    return z;
+}
+
+simm_status spike_prepare(SpikeFactor& f, hipStream_t st) {
+    f.n16 = (f.n + 15) / 16 * 16;
+    if (f.n16 > f.n) hipLaunchKernelGGL(k_pad_ipiv, dim3(1), dim3(16), 0, st, f.n, f.n16, f.ipiv);
+    // effective upper bandwidth of U: ku plus the largest interchange distance
+    int* d_jump = nullptr;
+    SIMM_HIP_TRY(device_malloc_ordered((void**)&d_jump, sizeof(int), st));
+    hipLaunchKernelGGL(k_max_jump, dim3(1), dim3(256), 0, st, f.n, (const int*)f.ipiv, d_jump);
+    int jump = 0;
+    SIMM_HIP_TRY(hipMemcpyAsync(&jump, d_jump, sizeof(int), hipMemcpyDeviceToHost, st));
+    SIMM_HIP_TRY(hipStreamSynchronize(st));
+    device_free_ordered(d_jump, st);
+    f.K = (int)std::min<int64_t>(std::min<int64_t>(f.kl + f.ku, f.ku + std::max(0, jump)), f.n - 1);
+    f.K = std::max(f.K, 1);
+    f.klx = std::max(1, (int)std::min<int64_t>(f.kl, f.n - 1));
+    if (f.n > (int64_t)1 << 30) {
+        set_error("order above 2^30 is not supported by the partitioned sweeps");
+        return SIMM_EUNSUPPORTED;
+    }
+    if (f.klx + 16 > 1024 || f.K + 16 > 1024) {
+        set_error("band too wide for the partitioned sweeps (bandwidth + 16 > 1024)");
+        return SIMM_EUNSUPPORTED;
+    }
+    sweep_layout(f);
+    f.Wf = chunk_threads(f.klx + 16);
+    f.Wb = chunk_threads(f.K + 16);
+    const int kl = f.klx, K = f.K;
+    const int64_t n16 = f.n16;
+    const SweepSizes z = sweep_sizes(f);
+    const size_t psi = z.psi, inner = z.inner, perms = z.perms;
+    SIMM_HIP_TRY(device_malloc(&f.mem, z.bytes));
     char* p = reinterpret_cast<char*>(f.mem);
     auto take_b = [&](size_t bytes) {
         char* r = p;
@@ -1425,6 +1444,26 @@ simm_status spike_clone_scratch(const SpikeFactor& base, SpikeFactor& out, hipSt
     hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(256), 0, st, out.counter, (int)((base.G + 1) * SPIKE_CTR_STRIDE), 0u);
     SIMM_HIP_TRY(hipGetLastError());
     return SIMM_OK;
+}
+
+size_t spike_prepare_bytes(int64_t n, int kl, int ku, int64_t bs, bool f32) {
+    SpikeFactor f;
+    f.n = n;
+    f.n16 = (n + 15) / 16 * 16;
+    f.kl = kl;
+    f.ku = ku;
+    f.f32 = f32;
+    f.bs = bs;
+    f.K = (int)std::max<int64_t>(1, std::min<int64_t>(kl + ku, n - 1));
+    f.klx = std::max(1, (int)std::min<int64_t>(kl, n - 1));
+    sweep_layout(f);
+    size_t bytes = sweep_sizes(f).bytes;
+    if (bs > 0) {
+        const size_t w = (size_t)(kl + ku);
+        const size_t scratch = sizeof(cplx) * w * ((size_t)f.n16 + 2 * (size_t)f.P * (f.klx + f.K));
+        bytes += part_prepare_bytes(n, kl, ku, bs, scratch);
+    }
+    return bytes;
 }
 
 void spike_release_ordered(SpikeFactor& f, hipStream_t st) {

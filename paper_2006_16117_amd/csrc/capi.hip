@@ -224,6 +224,13 @@ bool may_keep(int dev, size_t size, BlockList& evicted) {
     return c.bytes + size <= limit;
 }
 
+// Device memory of blocks kept or waiting to be freed.
+size_t spare_bytes() {
+    BlockCache& c = cache();
+    std::lock_guard<std::mutex> lk(c.mu);
+    return c.bytes + c.waiting_bytes;
+}
+
 // The block at q, taken from those handed out (into v, empty if it is not one of them).
 void take_block(void* q, BlockList& v) {
     BlockCache& c = cache();
@@ -1681,11 +1688,28 @@ struct AheadBuild {
     ~AheadBuild() { finish(); }
 };
 
+// Krylov phases that the association runs ahead of the cell order.
+// For small factors the Krylov phases of the next ones predicted to need a
+// shift run ahead too, on the factor's own stream, so that one shift's Krylov
+// phase overlaps the next's.  A small factor's Krylov phase is a chain of short launches
+// on a few compute units, and two of them share the device well (n = 400 band of
+// 45 KB: shift builds 450 -> 148 ms); a large one streams its factor through many
+// units per application, and beside the factors computed ahead two of them slowed
+// each other more than they overlapped (n = 40,000 band of 385 MB: ~875 -> ~950 ms
+// per step), so they stay one at a time.
+int krylov_ahead(const simm_pencil_s* p) {
+    const double band_bytes =
+        16.0 * (double)(2 * std::max(p->kla, p->klb) + std::max(p->kua, p->kub) + 1) * (double)p->n;
+    return band_bytes <= 64.0 * (1 << 20) ? 2 : 0;
+}
+
 // Number of shift factors the association may compute ahead: the requested
 // look-ahead (default: one per hardware queue the HIP runtime gives the process,
 // GPU_MAX_HW_QUEUES, 4 unless set, less the run stream's and the side stream's, at
 // most 11; more streams than queues share a queue and run one after the other), cut
-// so that the factors take at most a quarter of the free device memory.
+// so that they take at most a quarter of the device memory that is free or kept for reuse:
+// the factors themselves, and the sweep data of the one predicted next and of those whose
+// Krylov phases run ahead.
 int lookahead_width(const simm_params* prm, const simm_pencil_s* p) {
     int w = prm->lookahead;
     if (w <= 0) {
@@ -1698,9 +1722,13 @@ int lookahead_width(const simm_params* prm, const simm_pencil_s* p) {
     if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return 1;
     const int64_t n = p->n;
     const int kl = std::max(p->kla, p->klb), ku = std::max(p->kua, p->kub);
-    const double per_shift = 16.0 * ((double)(2 * kl + ku + 1) * n + (double)band_lu_panel_elems(n, kl) +
-                                     4.0 * (double)n * (kl + 16)) * 1.25;
-    const double fit = (double)free_b / 4.0 / per_shift;
+    const bool f32 = prm->precision == SIMM_PREC_MIXED;
+    const int64_t bs = part_block_len(n, kl, ku);
+    const double lu = (f32 ? 8.0 : 16.0) * ((double)(2 * kl + ku + 1) * n + (double)band_lu_panel_elems(n, kl)) +
+                      (bs > 0 ? 16.0 * (double)part_cpl_elems(n, kl, ku, bs) : 0.0);
+    const double sweeps = (double)spike_prepare_bytes(n, kl, ku, bs, f32);
+    const double quarter = ((double)free_b + (double)spare_bytes()) / 4.0;
+    const double fit = (quarter - (1 + krylov_ahead(p)) * sweeps) / lu;
     return (int)std::max(1.0, std::min((double)w, std::floor(fit)));
 }
 
@@ -1895,21 +1923,13 @@ simm_status associate(simm_pencil_s* p, const simm_params* prm, const cplx* f_de
             ++live;
         }
     };
-    // For small factors the Krylov phases of the next KA cells predicted to need a
-    // shift run ahead too, on the factor's own stream, so that one shift's Krylov
-    // phase overlaps the next's.  Prediction: the first cells after the current one
+    // The Krylov phases of the next KA cells predicted to need a
+    // shift run ahead too (krylov_ahead).  Prediction: the first cells after the current one
     // that no shift resolves so far, skipping the current cell's neighbours while new
     // shifts have mostly resolved their neighbours so far (then a neighbour rarely
     // needs a shift of its own).  A wrong guess costs a cancelled build, never a
-    // different result.  A small factor's Krylov phase is a chain of short launches
-    // on a few compute units, and two of them share the device well (n = 400 band of
-    // 45 KB: shift builds 450 -> 148 ms); a large one streams its factor through many
-    // units per application, and beside the factors computed ahead two of them slowed
-    // each other more than they overlapped (n = 40,000 band of 385 MB: ~875 -> ~950 ms
-    // per step), so they stay one at a time.
-    const double band_bytes =
-        16.0 * (double)(2 * std::max(p->kla, p->klb) + std::max(p->kua, p->kub) + 1) * (double)p->n;
-    const int KA = (W > 1 && band_bytes <= 64.0 * (1 << 20)) ? 2 : 0;
+    // different result.
+    const int KA = W > 1 ? krylov_ahead(p) : 0;
     if (KA > 0) {
         SIMM_HIP_TRY(hipEventCreateWithFlags(&ready, hipEventDisableTiming));
         SIMM_HIP_TRY(hipEventRecord(ready, st));

@@ -170,6 +170,8 @@ struct SpikeFactor {
 };
 int64_t spike_chunk_len(int64_t n, int kl, int K);
 simm_status spike_prepare(SpikeFactor& f, hipStream_t st);
+// device bytes spike_prepare takes at most (K = kl + ku), its own scratch included
+size_t spike_prepare_bytes(int64_t n, int kl, int ku, int64_t bs, bool f32);
 simm_status spike_apply(const SpikeFactor& f, const cplx* u, cplx* y, const int* active, hipStream_t st);
 // an application with D's factor alone (the whole factor when not partitioned)
 simm_status spike_apply_diag(const SpikeFactor& f, const cplx* u, cplx* y, const int* active, hipStream_t st);
@@ -206,6 +208,8 @@ constexpr int64_t kPartMaxReduced = 4096;   // largest reduced order (its invers
 int spike_block_chunks(int64_t bs, int64_t nbk, int kl, int K, double* us);
 // block length of the partitioned factorization of an order-n band (0: factor it whole)
 int64_t part_block_len(int64_t n, int kl, int ku);
+// device bytes of part_prepare: spikes, reduced inverse, and the larger of the two steps' scratch
+size_t part_prepare_bytes(int64_t n, int kl, int ku, int64_t bs, size_t spike_scratch);
 // copies the couplings of the diagonal blocks out of the assembled band (into cpl,
 // nbk - 1 boundaries of ku^2 + kl^2 entries) and zeroes them there
 simm_status part_cut(int64_t n, int kl, int ku, cplx* AB, int64_t bs, cplx* cpl, hipStream_t st);

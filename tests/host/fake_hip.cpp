@@ -87,7 +87,7 @@ T arg(void** a, int i) {
 struct Geometry {   // the first fields of the squares' geometry
     double x0, y0, w1;
 };
-// squares around the shift (level 1: within 1.6 cells) are resolved; of the squares of a
+// squares around the shift (level 1: within 1.2 cells) are resolved; of the squares of a
 // level those that hold one of a few fixed points are kept
 bool holds_point(const Geometry& g, int64_t level, int64_t ix, int64_t iy) {
     const double w = std::ldexp(g.w1, (int)(1 - level));

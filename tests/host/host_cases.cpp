@@ -198,6 +198,35 @@ static void sizes_in_use_are_kept() {
     simm_pencil_destroy(held);
 }
 
+// Factors are computed ahead of a run's order only where a quarter of the free memory holds
+// them with the sweep data of the next one (a wide band's: with spikes and reduced inverse).
+static void factors_ahead_fit() {
+    FakeHip& h = fake_hip();
+    const int64_t n = 24000;
+    const std::vector<double> f = ones(n);
+    simm_pencil p = band(n, 200, 200);
+    const size_t base = h.used;
+    simm_shift s = nullptr;
+    CHECK(simm_shift_build(p, 0.1, 0.2, f.data(), SIMM_MEM_HOST, 2, SIMM_PREC_FP64, nullptr, &s) == SIMM_OK);
+    simm_shift_destroy(s);
+    const size_t one = h.peak - base;   // a factor and its sweep data, while they are made
+    simm_params q = run_params(SIMM_FLAG_RELEASE_FACTORS, 8);
+    q.m = 2;
+    for (const double quarter : {0.95, 1.9}) {
+        simm_pencil_destroy(p);
+        p = band(n, 200, 200);
+        h.total = base + (size_t)(4 * quarter * (double)one);
+        const long made = h.streams_made;
+        simm_result r = nullptr;
+        CHECK(simm_run(p, &q, f.data(), SIMM_MEM_HOST, nullptr, &r) == SIMM_OK);
+        simm_result_destroy(r);
+        const long ahead = h.streams_made - made - 1;   // (one for the Schur forms)
+        std::printf("a quarter holds %.2f builds: %ld streams for factors ahead\n", quarter, ahead);
+        CHECK(quarter < 1 ? ahead == 0 : ahead > 1);
+    }
+    simm_pencil_destroy(p);
+}
+
 // The threads a run starts beside its own free nothing to the device (its memory is large
 // enough); what they release is freed by the run's thread.
 static void helpers_free_nothing() {
@@ -266,6 +295,7 @@ int main(int argc, char** argv) {
         {"batch_keeps_nothing", batch_keeps_nothing},
         {"kept_while_a_quarter_is_free", kept_while_a_quarter_is_free},
         {"sizes_in_use_are_kept", sizes_in_use_are_kept},
+        {"factors_ahead_fit", factors_ahead_fit},
         {"helpers_free_nothing", helpers_free_nothing},
         {"no_threads", no_threads},
         {"no_host_memory", no_host_memory},
