@@ -13,7 +13,6 @@
 #include <atomic>
 #include <chrono>
 #include <functional>
-#include <list>
 #include <unordered_map>
 #include <string>
 #include <thread>
@@ -89,8 +88,8 @@ struct JoinThreads {
 // a wait for the stream whose work used it (device_free_ordered), so any stream may take it.
 // (No events: they would be queried after their streams, which runs make and destroy, are
 // gone; and no device-wide wait for want of room while a run's threads are at work,
-// RunInFlight.)  Kept blocks are at most an eighth of the device's memory; the sizes not
-// asked for the longest make room for others.  What is free is looked at for every block of
+// RunInFlight.)  Kept blocks are at most an eighth of the device's memory; those kept the
+// longest make room for others.  What is free is looked at for every block of
 // 64 MB and whenever 64 MB have been kept since: less than a quarter, and all kept blocks are
 // given back, as they are when the last pencil and shift are gone or an allocation fails.
 //
@@ -100,7 +99,7 @@ struct JoinThreads {
 // the cache and the idle list below; the cause was not found, so batches are off both.
 //
 // Frees run in destructors: a block's entry is made when it is allocated and moves between the
-// lists by splicing, so that no free allocates host memory or throws.
+// tables as a node, so that no free allocates host memory or throws.
 namespace {
 thread_local bool t_batch = false;
 struct BatchThread {
@@ -114,42 +113,30 @@ struct BatchThread {
 // Threads that a call starts beside its own.
 thread_local bool t_helper = false;
 
-struct Block;
-using BlockList = std::list<Block>;
-struct SizeClass {
-    BlockList kept;
-    uint64_t asked = 0;   // BlockCache::clock at the last request of this size
-};
 struct Block {
     enum Kind { CACHED, PLAIN, ORDERED };   // the cache's; hipMalloc's; hipMallocAsync's
     void* p;
     int dev;
     size_t bytes;
     Kind kind;
-    SizeClass* cls;   // of a cached one
+    uint64_t kept_at;   // BlockCache::clock when it was kept
 };
+using Blocks = std::multimap<std::pair<int, size_t>, Block>;   // by device and size
+using BlockNode = Blocks::node_type;
 struct BlockCache {
     std::mutex mu;
-    std::map<std::pair<int, size_t>, SizeClass> classes;      // by device and size
-    BlockList out;                                            // handed out
-    std::unordered_map<void*, BlockList::iterator> find;      // of those
-    BlockList waiting;                                        // to be freed (DeferFrees)
+    Blocks kept;
+    Blocks waiting;                                           // to be freed (DeferFrees)
+    std::unordered_map<void*, BlockNode> out;                 // handed out
     size_t bytes = 0, waiting_bytes = 0;                      // of the blocks kept and waiting
     size_t unchecked = 0;                                     // kept since free memory was looked at
-    uint64_t clock = 0;                                       // requests
+    uint64_t clock = 0;                                       // blocks kept so far
     int live = 0;                                             // pencils and shifts
 };
 // (never destroyed: objects may outlive the library's own static data)
 BlockCache& cache() {
     static BlockCache* c = new BlockCache;
     return *c;
-}
-
-// Sizes in steps of an eighth of a power of two, so that blocks of nearly equal factors match.
-size_t block_size(size_t bytes) {
-    size_t step = 256;
-    while (step * 16 <= bytes) step *= 2;
-    return (std::max<size_t>(bytes, 1) + step - 1) / step * step;
 }
 
 struct DeviceGuard {
@@ -169,20 +156,19 @@ constexpr size_t kDeferBytes = (size_t)16 << 30;
 
 // Takes all kept blocks out and frees them (each hipFree waits for its device).
 void give_back_blocks() {
-    BlockList v;
+    Blocks v;
     {
         BlockCache& c = cache();
         std::lock_guard<std::mutex> lk(c.mu);
-        for (auto& kv : c.classes) v.splice(v.end(), kv.second.kept);
+        v.swap(c.kept);
         c.bytes = c.unchecked = 0;
     }
-    for (Block& b : v) (void)hipFree(b.p);
+    for (auto& kv : v) (void)hipFree(kv.second.p);
 }
 
-// Whether `size` more bytes may be kept on the current device.  Kept blocks of the sizes that
-// were not asked for the longest go where that makes room (into `evicted`, to be freed; not
-// while runs are in flight).
-bool may_keep(int dev, size_t size, BlockList& evicted) {
+// Whether `size` more bytes may be kept on the current device.  The blocks kept the longest go
+// where that makes room (into `evicted`, to be freed; not while runs are in flight).
+bool may_keep(int dev, size_t size, Blocks& evicted) {
     BlockCache& c = cache();
     const bool flying = g_runs.load() > 0;
     bool look;
@@ -213,13 +199,12 @@ bool may_keep(int dev, size_t size, BlockList& evicted) {
     }
     if (look) c.unchecked = 0;
     if (size > limit) return false;
-    while (c.bytes + size > limit && !flying) {
-        SizeClass* old = nullptr;
-        for (auto& kv : c.classes)
-            if (!kv.second.kept.empty() && (!old || kv.second.asked < old->asked)) old = &kv.second;
-        if (!old) break;
-        c.bytes -= old->kept.front().bytes;
-        evicted.splice(evicted.end(), old->kept, old->kept.begin());
+    while (c.bytes + size > limit && !flying && !c.kept.empty()) {
+        auto old = c.kept.begin();
+        for (auto q = c.kept.begin(); q != c.kept.end(); ++q)
+            if (q->second.kept_at < old->second.kept_at) old = q;
+        c.bytes -= old->second.bytes;
+        evicted.insert(c.kept.extract(old));
     }
     return c.bytes + size <= limit;
 }
@@ -231,46 +216,49 @@ size_t spare_bytes() {
     return c.bytes + c.waiting_bytes;
 }
 
-// The block at q, taken from those handed out (into v, empty if it is not one of them).
-void take_block(void* q, BlockList& v) {
+// The block at q, taken from those handed out (empty if it is not one of them).
+BlockNode take_block(void* q) {
     BlockCache& c = cache();
     std::lock_guard<std::mutex> lk(c.mu);
-    const auto it = c.find.find(q);
-    if (it == c.find.end()) return;
-    v.splice(v.end(), c.out, it->second);
-    c.find.erase(it);
+    BlockNode b;
+    const auto it = c.out.find(q);
+    if (it != c.out.end()) {
+        b = std::move(it->second);
+        c.out.erase(it);
+    }
+    return b;
 }
 
-void defer_free(BlockList& v);
+void defer_free(BlockNode b);
 void flush_deferred_frees();
 
-// One block nothing on the device uses any more: kept, or freed (a free waits for the whole
+// A block nothing on the device uses any more: kept, or freed (a free waits for the whole
 // device: with the others collected while runs are in flight).
-void keep_or_free(BlockList& v) {
-    Block& b = v.front();
-    BlockList evicted;
+void keep_or_free(BlockNode n) {
+    Block& b = n.mapped();
+    Blocks evicted;
     if (may_keep(b.dev, b.bytes, evicted)) {
         BlockCache& c = cache();
         std::lock_guard<std::mutex> lk(c.mu);
         c.bytes += b.bytes;
         c.unchecked += b.bytes;
-        b.cls->kept.splice(b.cls->kept.end(), v);
+        b.kept_at = ++c.clock;
+        c.kept.insert(std::move(n));
     } else if (g_runs.load() > 0) {
-        defer_free(v);
+        defer_free(std::move(n));
     } else {
         (void)hipFree(b.p);
     }
-    for (Block& e : evicted) (void)hipFree(e.p);
+    for (auto& kv : evicted) (void)hipFree(kv.second.p);
 }
 
 // Blocks that work on any stream may still use: one wait per device.  The cache's own are
 // freed outright, like the others, while a call has worker threads.
-void retire(BlockList& v) {
+void retire(Blocks& v) {
     int waited = -1;
     while (!v.empty()) {
-        BlockList one;
-        one.splice(one.end(), v, v.begin());
-        const Block& b = one.front();
+        BlockNode n = v.extract(v.begin());
+        const Block& b = n.mapped();
         DeviceGuard dg(b.dev);
         if (b.kind != Block::CACHED || g_runs.load() > 0) {
             (void)hipFree(b.p);
@@ -280,8 +268,17 @@ void retire(BlockList& v) {
             (void)hipDeviceSynchronize();
             waited = b.dev;
         }
-        keep_or_free(one);
+        keep_or_free(std::move(n));
     }
+}
+void retire_or_defer(BlockNode n) {
+    if (g_batches.load() > 0) {
+        defer_free(std::move(n));
+        return;
+    }
+    Blocks v;
+    v.insert(std::move(n));
+    retire(v);
 }
 
 // Streams of runs and their worker threads, non-blocking, kept for reuse while a pencil or
@@ -350,7 +347,7 @@ void object_gone() {
 // (one wait instead of one per block), and at its end: by the call's own thread, except in
 // batches, whose threads have no call's work beside them, and where memory ran out (new_block).
 void flush_deferred_frees() {
-    BlockList v;
+    Blocks v;
     {
         BlockCache& c = cache();
         std::lock_guard<std::mutex> lk(c.mu);
@@ -359,46 +356,45 @@ void flush_deferred_frees() {
     }
     retire(v);
 }
-void defer_free(BlockList& v) {
+void defer_free(BlockNode n) {
     bool flush = false;
     {
         BlockCache& c = cache();
         std::lock_guard<std::mutex> lk(c.mu);
-        for (Block& b : v) c.waiting_bytes += b.bytes;
-        c.waiting.splice(c.waiting.end(), v);
+        c.waiting_bytes += n.mapped().bytes;
+        c.waiting.insert(std::move(n));
         flush = c.waiting_bytes >= kDeferBytes && (t_batch || !t_helper);
     }
     flush |= g_batches.load() == 0;   // the last DeferFrees ended meanwhile
     if (flush) flush_deferred_frees();
 }
 
-// Hands out a block: a kept one of its size (CACHED), or a new one from `alloc`; when the
-// device is out of memory, the frees collected so far are done, the kept blocks given back
-// and the allocation is tried once more.
+// Hands out a block: a kept one (CACHED) of the size asked for or up to an eighth larger, so
+// that those of nearly equal factors match, or a new one from `alloc`; when the device is out
+// of memory, the frees collected so far are done, the kept blocks given back and the allocation
+// is tried once more.
 template <typename Alloc>
 hipError_t new_block(void** p, size_t bytes, Block::Kind kind, Alloc alloc) {
     *p = nullptr;
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
+    bytes = std::max<size_t>((bytes + 255) / 256 * 256, 256);
     BlockCache& c = cache();
-    BlockList one;   // the entry, made before the memory
-    one.push_back(Block{nullptr, dev, bytes, kind, nullptr});
-    Block& b = one.front();
     if (kind == Block::CACHED) {
         std::lock_guard<std::mutex> lk(c.mu);
-        SizeClass& s = c.classes[std::make_pair(dev, bytes)];
-        s.asked = ++c.clock;
-        if (!s.kept.empty()) {
-            const auto it = std::prev(s.kept.end());
-            c.find.emplace(it->p, it);
-            c.out.splice(c.out.end(), s.kept, it);
-            c.bytes -= bytes;
-            *p = it->p;
+        const auto it = c.kept.lower_bound(std::make_pair(dev, bytes));
+        if (it != c.kept.end() && it->second.dev == dev && it->second.bytes - bytes <= bytes / 8) {
+            void* const q = it->second.p;
+            BlockNode& entry = c.out[q];
+            c.bytes -= it->second.bytes;
+            entry = c.kept.extract(it);
+            *p = q;
             return hipSuccess;
         }
-        b.cls = &s;
     }
+    Blocks made;   // the entry, before the memory
+    Block& b = made.emplace(std::make_pair(dev, bytes), Block{nullptr, dev, bytes, kind, 0})->second;
     e = alloc(&b.p, bytes);
     if (e == hipErrorOutOfMemory) {
         (void)hipGetLastError();
@@ -406,12 +402,14 @@ hipError_t new_block(void** p, size_t bytes, Block::Kind kind, Alloc alloc) {
         give_back_blocks();
         e = alloc(&b.p, bytes);
     }
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess) {
+        (void)hipGetLastError();   // (the caller has the error; the next launch must not find it)
+        return e;
+    }
     void* const q = b.p;
     try {
         std::lock_guard<std::mutex> lk(c.mu);
-        c.find.emplace(q, one.begin());
-        c.out.splice(c.out.end(), one);
+        c.out[q] = made.extract(made.begin());
     } catch (...) {
         (void)hipFree(q);
         throw;
@@ -423,42 +421,36 @@ hipError_t new_block(void** p, size_t bytes, Block::Kind kind, Alloc alloc) {
 
 void release_device(void* q) {
     if (!q) return;
-    BlockList v;
-    take_block(q, v);
-    if (g_batches.load() == 0) retire(v);
-    else defer_free(v);
+    BlockNode n = take_block(q);
+    if (!n.empty()) retire_or_defer(std::move(n));
 }
 
 hipError_t device_malloc(void** p, size_t bytes) {
-    const auto alloc = [](void** q, size_t b) { return hipMalloc(q, b); };
-    if (t_batch) return new_block(p, std::max<size_t>(bytes, 1), Block::PLAIN, alloc);
-    return new_block(p, block_size(bytes), Block::CACHED, alloc);
+    return new_block(p, bytes, t_batch ? Block::PLAIN : Block::CACHED,
+                     [](void** q, size_t b) { return hipMalloc(q, b); });
 }
 
 // A block that only work on st will use, to be freed with device_free_ordered on st.
 hipError_t device_malloc_ordered(void** p, size_t bytes, hipStream_t st) {
     if (!t_batch) return device_malloc(p, bytes);
-    return new_block(p, std::max<size_t>(bytes, 1), Block::ORDERED,
-                     [st](void** q, size_t b) { return hipMallocAsync(q, b, st); });
+    return new_block(p, bytes, Block::ORDERED, [st](void** q, size_t b) { return hipMallocAsync(q, b, st); });
 }
 
 // Frees a block that only work on st has used: in st's order (a batch's), or after a wait for
 // st, not for the device.
 void device_free_ordered(void* q, hipStream_t st) {
     if (!q) return;
-    BlockList v;
-    take_block(q, v);
-    if (v.empty()) return;
-    const Block& b = v.front();
+    BlockNode n = take_block(q);
+    if (n.empty()) return;
+    const Block& b = n.mapped();
     if (b.kind == Block::ORDERED) {
         (void)hipFreeAsync(b.p, st);
     } else if (b.kind == Block::CACHED && hipStreamSynchronize(st) == hipSuccess) {
         DeviceGuard dg(b.dev);
-        keep_or_free(v);
+        keep_or_free(std::move(n));
     } else {
         (void)hipGetLastError();
-        if (g_batches.load() == 0) retire(v);
-        else defer_free(v);
+        retire_or_defer(std::move(n));
     }
 }
 

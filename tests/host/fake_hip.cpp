@@ -244,7 +244,7 @@ int hipMalloc(void** p, size_t bytes) {
     Inside in;
     std::lock_guard<std::mutex> lk(t().mu);
     t().state.mallocs += 1;
-    t().state.largest = std::max(t().state.largest, bytes);
+    t().state.watched += bytes == t().state.watch;
     if (t().state.used + bytes > t().state.total) return *p = nullptr, 2;
     void* q = mmap(nullptr, bytes, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
     if (q == MAP_FAILED) return *p = nullptr, 2;

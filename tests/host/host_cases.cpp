@@ -227,6 +227,26 @@ static void factors_ahead_fit() {
     simm_pencil_destroy(p);
 }
 
+// Blocks take what is asked for, so that what fits without a cache fits with it; one that is
+// kept serves requests down to eight ninths of its size.
+static void blocks_have_the_size_asked_for() {
+    FakeHip& h = fake_hip();
+    const int64_t n = 33000;
+    const std::vector<double> f = ones(n);
+    simm_pencil p = band(n, 8, 8);
+    h.watch = 16 * (size_t)n * 100;   // the basis
+    simm_shift s = nullptr;
+    CHECK(simm_shift_build(p, 0.1, 0.2, f.data(), SIMM_MEM_HOST, 99, SIMM_PREC_FP64, nullptr, &s) == SIMM_OK);
+    CHECK(h.watched == 1);
+    simm_shift_destroy(s);
+    build_one(60000);
+    const long before = h.mallocs;
+    build_one(59900);
+    std::printf("%ld allocations\n", h.mallocs - before);
+    CHECK(h.mallocs == before);
+    simm_pencil_destroy(p);
+}
+
 // The threads a run starts beside its own free nothing to the device (its memory is large
 // enough); what they release is freed by the run's thread.
 static void helpers_free_nothing() {
@@ -296,6 +316,7 @@ int main(int argc, char** argv) {
         {"kept_while_a_quarter_is_free", kept_while_a_quarter_is_free},
         {"sizes_in_use_are_kept", sizes_in_use_are_kept},
         {"factors_ahead_fit", factors_ahead_fit},
+        {"blocks_have_the_size_asked_for", blocks_have_the_size_asked_for},
         {"helpers_free_nothing", helpers_free_nothing},
         {"no_threads", no_threads},
         {"no_host_memory", no_host_memory},
