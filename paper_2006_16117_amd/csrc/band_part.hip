@@ -794,7 +794,15 @@ simm_status spikes(const SpikeFactor& f, hipStream_t st) {
     const int64_t n16 = f.n16;
     SpikeFactor cl;
     // (freed in st's order: a plain free would wait for the whole device)
-    SIMM_TRY(spike_clone_scratch(f, cl, st, f.cbs > 0 ? w : spike_max_nrhs(f), true));
+    // scratch of all columns, which is as much as the spikes themselves; of fewer at a time where
+    // memory does not hold it
+    int cols = f.cbs > 0 ? w : spike_max_nrhs(f);
+    for (;;) {
+        const simm_status rc = spike_clone_scratch(f, cl, st, cols, true);
+        if (rc == SIMM_OK) break;
+        if (rc != SIMM_ENOMEM || cols == 1) return rc;
+        cols = (cols + 1) / 2;
+    }
     struct Release {
         SpikeFactor* c;
         hipStream_t st;

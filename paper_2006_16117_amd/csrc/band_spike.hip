@@ -1734,15 +1734,12 @@ simm_status spike_apply_diag_nr(const SpikeFactor& f, const cplx* u, int64_t ldu
 simm_status spike_apply_diag_cols(const SpikeFactor& f, cplx* X, int cols, hipStream_t st) {
     // groups of spike_max_nrhs columns (inside blocks: all groups in the same launches), then
     // the remainder one by one; every launch uses the scratch from its start (stream order)
+    // (as many of them as the scratch holds)
     const int nrmax = spike_max_nrhs(f);
     for (int c0 = 0; c0 < cols;) {
         int nr = nrmax;
-        while (nr > cols - c0) nr /= 2;
-        const int groups = f.cbs > 0 ? (cols - c0) / nr : 1;
-        if (groups * nr > f.nrhs) {
-            set_error("scratch for fewer columns than asked for");
-            return SIMM_EINVAL;
-        }
+        while (nr > std::min(cols - c0, f.nrhs)) nr /= 2;
+        const int groups = f.cbs > 0 ? std::min(cols - c0, f.nrhs) / nr : 1;
         cplx* x = X + (int64_t)c0 * f.n16;
         if (f.f32)
             SIMM_TRY(apply_t<cplxf>(f, f.Gf32, f.Hb32, f.PsiL32, f.PsiU32, x, x, nullptr, st, nr, f.n16, f.n16, groups, true));

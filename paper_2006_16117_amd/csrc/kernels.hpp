@@ -176,7 +176,8 @@ simm_status spike_apply(const SpikeFactor& f, const cplx* u, cplx* y, const int*
 // an application with D's factor alone (the whole factor when not partitioned)
 simm_status spike_apply_diag(const SpikeFactor& f, const cplx* u, cplx* y, const int* active, hipStream_t st);
 // D^{-1} of `cols` columns of a partitioned factor in as few launches as a single one
-// takes, in place (X: n16 x cols); scratch from spike_clone_scratch(..., cols, true)
+// takes, in place (X: n16 x cols); scratch from spike_clone_scratch(..., cols, true), or of
+// fewer columns, which are then taken at a time
 simm_status spike_apply_diag_cols(const SpikeFactor& f, cplx* X, int cols, hipStream_t st);
 // the same for nr right-hand sides at once (columns u + r ldu -> y + r ldy, r < nr), each
 // column computed exactly as spike_apply_diag computes it; nr <= f.nrhs and

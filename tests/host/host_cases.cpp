@@ -247,6 +247,38 @@ static void blocks_have_the_size_asked_for() {
     simm_pencil_destroy(p);
 }
 
+// Scratch of the spikes' columns: of all of them where memory holds it, else of fewer at a
+// time, and the factor stays partitioned.
+static void spikes_with_less_scratch() {
+    FakeHip& h = fake_hip();
+    const int64_t n = 1 << 18, w = 128;
+    const std::vector<double> f = ones(n);
+    const size_t all = h.total;
+    auto build = [&](size_t memory, int64_t* block) {
+        h.total = memory;
+        simm_pencil p = band(n, w / 2, w / 2);
+        simm_shift s = nullptr;
+        h.peak = 0;
+        const simm_status rc = simm_shift_build(p, 0.1, 0.2, f.data(), SIMM_MEM_HOST, 2, SIMM_PREC_FP64, nullptr, &s);
+        *block = 0;
+        if (rc == SIMM_OK) CHECK(simm_shift_factor_info(s, block, nullptr, nullptr) == SIMM_OK);
+        simm_shift_destroy(s);
+        simm_pencil_destroy(p);
+        return rc;
+    };
+    int64_t block = 0;
+    CHECK(build(all, &block) == SIMM_OK && block > 0);
+    const size_t peak = h.peak, scratch = 16 * (size_t)n * w;
+    size_t lo = h.peak / 2, hi = h.peak;   // the least memory of a partitioned factor
+    while (hi - lo > scratch / 64) {
+        const size_t mid = (lo + hi) / 2;
+        (build(mid, &block) == SIMM_OK && block > 0 ? hi : lo) = mid;
+    }
+    std::printf("%.0f MB are enough, %.0f MB taken where there is more, scratch %.0f MB\n", hi / 1e6, peak / 1e6,
+                scratch / 1e6);
+    CHECK(hi + 9 * scratch / 10 < peak);
+}
+
 // The threads a run starts beside its own free nothing to the device (its memory is large
 // enough); what they release is freed by the run's thread.
 static void helpers_free_nothing() {
@@ -317,6 +349,7 @@ int main(int argc, char** argv) {
         {"sizes_in_use_are_kept", sizes_in_use_are_kept},
         {"factors_ahead_fit", factors_ahead_fit},
         {"blocks_have_the_size_asked_for", blocks_have_the_size_asked_for},
+        {"spikes_with_less_scratch", spikes_with_less_scratch},
         {"helpers_free_nothing", helpers_free_nothing},
         {"no_threads", no_threads},
         {"no_host_memory", no_host_memory},
