@@ -190,7 +190,8 @@ simm_status simm_shift_refine_stats(simm_shift s, int64_t* solves, int64_t* corr
  * columns factored side by side with partial pivoting inside each block, the couplings
  * solved through the spikes' reduced system); 0: one band LU of the whole matrix.
  * fallback = 1 when a partitioned factor was replaced by the whole-matrix one (a singular
- * diagonal block or reduced system, or a solve's normwise backward error above 1e-13);
+ * diagonal block or reduced system, a solve's normwise backward error above 1e-13, or memory
+ * that does not hold the partitioned factor's sweep data);
  * eta: that backward error of the partitioned FP64 factor (-1 when not measured).  The
  * library partitions bands with kl, ku >= 1 and kl + ku <= 512 of orders that give
  * blocks of at least max(256, 4 (kl + ku)) rows (1024 for kl + ku > 128), with at most

@@ -584,23 +584,28 @@ struct simm_shift_s {
         DeferFrees together(true);
         release_device(spike.mem);
         release_device(spike.part_mem);
+        release_lu();
+        release_device(ref_mem);
+        spike = SpikeFactor{};
+        ref_mem = nullptr;
+        rst = RefineState{};
+        mixed_stats_saved = true;
+    }
+    // frees the LU factor
+    void release_lu() {
+        DeferFrees together(true);
         release_device(CPL);
-        CPL = nullptr;
         release_device(AB);
         release_device(ipiv);
         release_device(LP);
         release_device(AB32);
         release_device(LP32);
-        release_device(ref_mem);
-        spike = SpikeFactor{};
+        CPL = nullptr;
         AB = nullptr;
         ipiv = nullptr;
         LP = nullptr;
         AB32 = nullptr;
         LP32 = nullptr;
-        ref_mem = nullptr;
-        rst = RefineState{};
-        mixed_stats_saved = true;
     }
     bool has_factor() const { return (AB != nullptr || AB32 != nullptr) && V != nullptr; }
     // the factor's data for a Krylov space built on it by another (borrowing) shift
@@ -1041,7 +1046,7 @@ simm_status prepare_sweeps(simm_shift_s* s, hipStream_t st, KernelClock* clk = n
         KScope ks(clk, SIMM_K_SPIKE_PREP);
         rc = spike_prepare(s->spike, st);
     }
-    if (rc != SIMM_OK && !(s->part_bs > 0 && rc == SIMM_ESINGULAR_SHIFT)) return rc;
+    if (rc != SIMM_OK && !(s->part_bs > 0 && (rc == SIMM_ESINGULAR_SHIFT || rc == SIMM_ENOMEM))) return rc;
     bool redo = rc != SIMM_OK;
     if (!redo && s->part_bs > 0 && !s->mixed) {
         // pivoting stays inside the blocks: the partitioned factor is kept only if a
@@ -1059,9 +1064,12 @@ simm_status prepare_sweeps(simm_shift_s* s, hipStream_t st, KernelClock* clk = n
         // the whole-matrix factor instead, in place of the partitioned one
         std::unique_ptr<simm_shift_s> w;
         SIMM_HIP_TRY(hipStreamSynchronize(st));
-        SIMM_TRY(factor_shift(s->p, s->sigma, st, w, clk, nullptr, s->mixed ? SIMM_PREC_MIXED : SIMM_PREC_FP64, true));
+        // (its memory first: where the partitioned factor does not fit, the whole one may, which
+        // has no spikes and no reduced inverse)
         spike_release(s->spike);
         s->spike = SpikeFactor{};
+        s->release_lu();
+        SIMM_TRY(factor_shift(s->p, s->sigma, st, w, clk, nullptr, s->mixed ? SIMM_PREC_MIXED : SIMM_PREC_FP64, true));
         std::swap(s->AB, w->AB);
         std::swap(s->AB32, w->AB32);
         std::swap(s->LP, w->LP);

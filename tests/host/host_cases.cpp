@@ -279,6 +279,36 @@ static void spikes_with_less_scratch() {
     CHECK(hi + 9 * scratch / 10 < peak);
 }
 
+// A band that is partitioned is factored whole where memory holds only that.
+static void whole_factor_where_it_fits() {
+    FakeHip& h = fake_hip();
+    const int64_t n = 24000;
+    const std::vector<double> f = ones(n);
+    auto build = [&](size_t memory, int64_t* block, int32_t* fallback) {
+        h.total = memory;
+        simm_pencil p = band(n, 200, 200);
+        simm_shift s = nullptr;
+        h.peak = 0;
+        const simm_status rc = simm_shift_build(p, 0.1, 0.2, f.data(), SIMM_MEM_HOST, 2, SIMM_PREC_FP64, nullptr, &s);
+        if (rc == SIMM_OK) CHECK(simm_shift_factor_info(s, block, fallback, nullptr) == SIMM_OK);
+        simm_shift_destroy(s);
+        simm_pencil_destroy(p);
+        return rc;
+    };
+    const size_t all = h.total;
+    int64_t block = 0;
+    int32_t fallback = 0;
+    CHECK(build(all, &block, &fallback) == SIMM_OK && block > 0 && fallback == 0);
+    setenv("SIMM_LU_PART", "0", 1);
+    CHECK(build(all, &block, &fallback) == SIMM_OK && block == 0);
+    const size_t whole = h.peak;
+    CHECK(build(whole, &block, &fallback) == SIMM_OK);
+    unsetenv("SIMM_LU_PART");
+    const simm_status rc = build(whole, &block, &fallback);
+    std::printf("%.0f MB: %s\n", whole / 1e6, rc == SIMM_OK ? "ok" : simm_last_error());
+    CHECK(rc == SIMM_OK && block == 0 && fallback == 1);
+}
+
 // The threads a run starts beside its own free nothing to the device (its memory is large
 // enough); what they release is freed by the run's thread.
 static void helpers_free_nothing() {
@@ -350,6 +380,7 @@ int main(int argc, char** argv) {
         {"factors_ahead_fit", factors_ahead_fit},
         {"blocks_have_the_size_asked_for", blocks_have_the_size_asked_for},
         {"spikes_with_less_scratch", spikes_with_less_scratch},
+        {"whole_factor_where_it_fits", whole_factor_where_it_fits},
         {"helpers_free_nothing", helpers_free_nothing},
         {"no_threads", no_threads},
         {"no_host_memory", no_host_memory},
