@@ -1752,6 +1752,10 @@ simm_status spike_apply_diag_cols(const SpikeFactor& f, cplx* X, int cols, hipSt
 
 simm_status spike_apply_nr(const SpikeFactor& f, const cplx* u, int64_t ldu, cplx* y, int64_t ldy, int nr,
                            hipStream_t st) {
+    if (nr == 3) {   // (the kernels take 1, 2 or 4)
+        SIMM_TRY(spike_apply_nr(f, u, ldu, y, ldy, 2, st));
+        return spike_apply_nr(f, u + 2 * ldu, ldu, y + 2 * ldy, ldy, 1, st);
+    }
     if (f.bs > 0) return part_apply_nr(f, u, ldu, y, ldy, nr, st);
     return spike_apply_diag_nr(f, u, ldu, y, ldy, nr, st);
 }

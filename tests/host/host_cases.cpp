@@ -309,6 +309,30 @@ static void whole_factor_where_it_fits() {
     CHECK(rc == SIMM_OK && block == 0 && fallback == 1);
 }
 
+// Blocks of three right-hand sides: three squares of a shift, three start vectors.
+static void three_at_once() {
+    const int64_t n = 500;
+    const std::vector<double> f = ones(3 * n);
+    simm_pencil p = band(n, 8, 8);
+    const simm_params q = run_params(0, 1);
+    simm_result r = nullptr;
+    CHECK(simm_run(p, &q, f.data(), SIMM_MEM_HOST, nullptr, &r) == SIMM_OK);
+    int64_t nc = 0;
+    simm_result_summary(r, nullptr, nullptr, &nc, nullptr);
+    std::vector<int32_t> mult((size_t)nc);
+    CHECK(simm_multiplicities(r, f.data(), 3, SIMM_MEM_HOST, 1e-6, nullptr, mult.data(), nullptr, nc) == SIMM_OK);
+    simm_shift s = nullptr;
+    CHECK(simm_result_shift(r, 0, &s) == SIMM_OK);
+    const int64_t squares[] = {1, 1, 1, 0, 1, 2, 1, 0, 1, 1, 2, 0, 1, 2, 2, 0, 2, 3, 3, 0, 2, 3, 4, 0, 2, 4, 4, 0};
+    double J = 0.0;
+    std::vector<double> grad((size_t)(2 * n));
+    for (int64_t count = 1; count <= 7; ++count)
+        CHECK(simm_gradient(&s, 1, squares, count, &q, 0, 0, nullptr, &J, nullptr, grad.data(), SIMM_MEM_HOST, nullptr) ==
+              SIMM_OK);
+    simm_result_destroy(r);
+    simm_pencil_destroy(p);
+}
+
 // The threads a run starts beside its own free nothing to the device (its memory is large
 // enough); what they release is freed by the run's thread.
 static void helpers_free_nothing() {
@@ -381,6 +405,7 @@ int main(int argc, char** argv) {
         {"blocks_have_the_size_asked_for", blocks_have_the_size_asked_for},
         {"spikes_with_less_scratch", spikes_with_less_scratch},
         {"whole_factor_where_it_fits", whole_factor_where_it_fits},
+        {"three_at_once", three_at_once},
         {"helpers_free_nothing", helpers_free_nothing},
         {"no_threads", no_threads},
         {"no_host_memory", no_host_memory},
