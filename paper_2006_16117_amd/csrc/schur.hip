@@ -40,8 +40,9 @@ namespace {
 __device__ inline int hoff(int j) { return j * (j + 5) / 2; }   // column j holds rows 0 .. j+2
 
 __device__ inline cplx csqrt_d(cplx z) {
-    // principal square root (entries of H_m are far from the double range limits)
-    const double r = sqrt(z.re * z.re + z.im * z.im);
+    // principal square root (z is of the size of H_m's entries squared: its own squares may leave
+    // the range that those of the entries stay in)
+    const double r = hypot(z.re, z.im);
     if (r == 0.0) return mk(0.0, 0.0);
     const double a = sqrt(0.5 * (r + fabs(z.re)));
     const double b = z.im / (2.0 * a);
