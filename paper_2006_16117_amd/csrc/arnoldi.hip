@@ -286,11 +286,20 @@ namespace {
 // launches fewer a step; every workgroup then reads all of them)
 constexpr int GS_SELF_BLOCKS = 64;
 
+// klb + kub from which B v_{j+1} is a launch of its own, by columns: a row's strided walk, with
+// a division per entry of v, costs more than the launch (a build of 60 steps at n = 100,000: 24
+// off-diagonals 15.5 and 15.2 ms, 32 17.0 and 16.3, 64 25.1 and 22.8; at n = 1,000 6.5 and 6.6,
+// 6.6 and 6.7, 7.3 and 7.0).
+constexpr int GS_WIDE_B = 32;
+
 simm_status gs_next(int64_t n, const GsBatch& b, int nr, int64_t ldv, int j, int ldh, int nblk, const cplx* Bb, int klb,
                     int kub, bool want_u, hipStream_t st) {
+    const bool wide = want_u && Bb != nullptr && klb + kub >= GS_WIDE_B;
     hipLaunchKernelGGL(k_gs_next, dim3((unsigned)((n + 255) / 256), (unsigned)nr), dim3(256), 0, st, n, b, ldv, j, ldh,
-                       nblk, nblk <= GS_SELF_BLOCKS ? 1 : 0, Bb, klb, kub, want_u ? 1 : 0);
+                       nblk, nblk <= GS_SELF_BLOCKS ? 1 : 0, Bb, klb, kub, want_u && !wide ? 1 : 0);
     SIMM_HIP_TRY(hipGetLastError());
+    for (int r = 0; wide && r < nr; ++r)
+        SIMM_TRY(prepare_input(n, b.V[r] + (int64_t)(j + 1) * ldv, Bb, klb, kub, b.u[r], st));
     return SIMM_OK;
 }
 }  // namespace
