@@ -102,24 +102,9 @@ __device__ inline int wave_min_int(int k) {
     return __builtin_amdgcn_readlane(k, 63);
 }
 
-__device__ inline cplx rdlane(cplx v, int l) { return cplx{rdlane_d(v.re, l), rdlane_d(v.im, l)}; }
-__device__ inline cplxf rdlane(cplxf v, int l) { return cplxf{rdlane_d(v.re, l), rdlane_d(v.im, l)}; }
 // value of the partner lane (lane xor 1)
 __device__ inline cplx swap_pair(cplx v) { return cplx{dpp_d<0xB1>(v.re), dpp_d<0xB1>(v.im)}; }
 __device__ inline cplxf swap_pair(cplxf v) { return cplxf{dpp_d<0xB1>(v.re), dpp_d<0xB1>(v.im)}; }
-
-// 16-byte (FP64) or 8-byte (FP32) LDS accesses of whole complex entries; every LDS
-// buffer below is aligned to its entry size.
-__device__ inline cplx ldsr(const cplx* p) {
-    const double2 v = *reinterpret_cast<const double2*>(p);
-    return cplx{v.x, v.y};
-}
-__device__ inline void ldsw(cplx* p, cplx v) { *reinterpret_cast<double2*>(p) = double2{v.re, v.im}; }
-__device__ inline cplxf ldsr(const cplxf* p) {
-    const float2 v = *reinterpret_cast<const float2*>(p);
-    return cplxf{v.x, v.y};
-}
-__device__ inline void ldsw(cplxf* p, cplxf v) { *reinterpret_cast<float2*>(p) = float2{v.re, v.im}; }
 
 template <typename C>
 struct Real;

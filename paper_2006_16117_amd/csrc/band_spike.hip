@@ -56,12 +56,6 @@ namespace {
 
 __device__ inline cplx ldz(const cplx* p, int64_t i, int64_t n) { return (i >= 0 && i < n) ? p[i] : mk(0.0, 0.0); }
 
-__device__ inline cplx ldsr(const cplx* p) {
-    const double2 v = *reinterpret_cast<const double2*>(p);
-    return cplx{v.x, v.y};
-}
-__device__ inline void ldsw(cplx* p, cplx v) { *reinterpret_cast<double2*>(p) = double2{v.re, v.im}; }
-
 // acc += sum_{q = 4 Q4}^{4 Q4 + 3} g_q t(lane q of the 16-lane row), four complex multiply-adds
 // whose second factor is the value that lane q of each row of 16 lanes holds: the multiply-add
 // broadcasts it itself (DPP row_newbcast), where a lane read per half of it took half the
@@ -76,7 +70,7 @@ __device__ __forceinline__ void fma_bcast4(cplx& acc, cplx t, cplx g0, cplx g1, 
     "v_fmac_f64_dpp %1, %2, " gi " row_newbcast:" q " row_mask:0xf bank_mask:0xf\n\t"
     asm("s_nop 1\n\t" SIMM_FMA_BCAST("%4", "%5", "%12") SIMM_FMA_BCAST("%6", "%7", "%13")
             SIMM_FMA_BCAST("%8", "%9", "%14") SIMM_FMA_BCAST("%10", "%11", "%15")
-        : "+v"(acc.re), "+v"(acc.im)
+        : "+&v"(acc.re), "+&v"(acc.im)
         : "v"(t.re), "v"(t.im), "v"(g0.re), "v"(g0.im), "v"(g1.re), "v"(g1.im), "v"(g2.re), "v"(g2.im), "v"(g3.re),
           "v"(g3.im), "n"(4 * Q4), "n"(4 * Q4 + 1), "n"(4 * Q4 + 2), "n"(4 * Q4 + 3));
 #undef SIMM_FMA_BCAST

@@ -90,6 +90,19 @@ __host__ __device__ inline cplx cdiv(cplx a, cplx b) {
 // ---------------------------------------------------------------------------
 __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// 16-byte (FP64) or 8-byte (FP32) LDS accesses of whole complex entries; every LDS
+// buffer is aligned to its entry size.
+__device__ inline cplx ldsr(const cplx* p) {
+    const double2 v = *reinterpret_cast<const double2*>(p);
+    return cplx{v.x, v.y};
+}
+__device__ inline void ldsw(cplx* p, cplx v) { *reinterpret_cast<double2*>(p) = double2{v.re, v.im}; }
+__device__ inline cplxf ldsr(const cplxf* p) {
+    const float2 v = *reinterpret_cast<const float2*>(p);
+    return cplxf{v.x, v.y};
+}
+__device__ inline void ldsw(cplxf* p, cplxf v) { *reinterpret_cast<float2*>(p) = float2{v.re, v.im}; }
+
 // ---------------------------------------------------------------------------
 // lane exchange within a wavefront (device code)
 // ---------------------------------------------------------------------------
@@ -110,6 +123,8 @@ __device__ inline double rdlane_d(double v, int l) {
     return __hiloint2double(hi, lo);
 }
 __device__ inline float rdlane_d(float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); }
+__device__ inline cplx rdlane(cplx v, int l) { return cplx{rdlane_d(v.re, l), rdlane_d(v.im, l)}; }
+__device__ inline cplxf rdlane(cplxf v, int l) { return cplxf{rdlane_d(v.re, l), rdlane_d(v.im, l)}; }
 
 // Maximum over the wavefront, returned to every lane: DPP within 16-lane rows
 // (quad xor 1, quad xor 2, half-row mirror, row mirror), then row broadcasts of

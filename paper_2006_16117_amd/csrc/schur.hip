@@ -57,19 +57,6 @@ __device__ inline double rsqrt_d(double a) {
     return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 
-__device__ inline double rdlane_d(double v, int l) {
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), l);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
-    return __hiloint2double(hi, lo);
-}
-__device__ inline cplx rdlane(cplx v, int l) { return cplx{rdlane_d(v.re, l), rdlane_d(v.im, l)}; }
-
-__device__ inline cplx ldsr(const cplx* p) {
-    const double2 v = *reinterpret_cast<const double2*>(p);
-    return cplx{v.x, v.y};
-}
-__device__ inline void ldsw(cplx* p, cplx v) { *reinterpret_cast<double2*>(p) = double2{v.re, v.im}; }
-
 constexpr int MAX_SCHUR_M = 128;
 constexpr size_t SCHUR_LDS = 160 * 1024;
 
