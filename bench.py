@@ -112,11 +112,11 @@ def apply_bytes(n: int, k: int, kb: int) -> int:
     return 16 * n * ((3 * k + 1) + (2 * kb + 1) + 6)
 
 
-def lu_flops_per_launch(kl: int, ku: int) -> int:
-    """Algorithmic flops of one panel launch of the band LU: 16 columns, each a
-    rank-1 update of kl rows by kl + ku columns (8 real flops per complex
-    multiply-add)."""
-    return LU_PANEL * 8 * kl * (kl + ku)
+def lu_flops_per_launch(kl: int, ku: int, blocks: int) -> int:
+    """Algorithmic flops of one panel launch of the band LU: 16 columns of every
+    diagonal block that is factored side by side, each a rank-1 update of kl rows by
+    kl + ku columns (8 real flops per complex multiply-add)."""
+    return blocks * LU_PANEL * 8 * kl * (kl + ku)
 
 
 def cpu_baseline(pen, f, params, n_qp, threads=0):
@@ -481,7 +481,10 @@ def main():
     n = pen.n
     kl, ku = max(pen.kl_a, pen.kl_b), max(pen.ku_a, pen.ku_b)
     kb = max(pen.kl_b, pen.ku_b) if pen.b_band is not None else 0
-    # dominant kernel: the band LU's panel step (one launch per 16 columns plus one)
+    # dominant kernel: the band LU's panel step (one launch per 16 columns plus one, of every
+    # diagonal block of a partitioned factor)
+    block_len = last.shift(0).factor_info()["block_len"]
+    lu_blocks = -(-n // block_len) if block_len else 1
     lu_launches = kcnt["band_lu"]   # panel launches (factors cancelled part-way included)
     lu_us_step = kms["band_lu"] * 1e3 / max(lu_launches, 1)
     # The step computes up to 11 factors at once (the level-1 association's look-ahead),
@@ -492,7 +495,7 @@ def main():
     lu_us = solo.kernel_ms["band_lu"] * 1e3 / max(solo.kernel_launches["band_lu"], 1)
     lu_solo_launches = solo.kernel_launches["band_lu"]
     del solo
-    lu_tflops = lu_flops_per_launch(kl, ku) / (lu_us * 1e-6) / 1e12
+    lu_tflops = lu_flops_per_launch(kl, ku, lu_blocks) / (lu_us * 1e-6) / 1e12
     # K2: one application of M (B v + partitioned L and U sweeps)
     b_apply = apply_bytes(n, max(kl, ku), kb)
     apply_ms = kms["band_sweep"] / max(kcnt["band_sweep"], 1)
@@ -530,14 +533,14 @@ def main():
             "hw_queues": HW_QUEUES,
         },
         "roofline": {
-            "kernel": "k_band_lu_step (one 16-column panel of the banded LU)",
+            "kernel": f"k_band_lu_step (one 16-column panel of the banded LU, {lu_blocks} blocks side by side)",
             "bound": "alu",
             "achieved": lu_tflops,
             "peak": FP64_PEAK_TFLOPS,
             "unit": "TFLOP/s",
             "frac": lu_tflops / FP64_PEAK_TFLOPS,
             "traffic": measured_traffic("k_band_lu_step_convdiff_n40000_traffic.md"),
-            "flops_per_launch": lu_flops_per_launch(kl, ku),
+            "flops_per_launch": lu_flops_per_launch(kl, ku, lu_blocks),
             "us_per_launch": lu_us,
             "launches_measured": lu_solo_launches,
             "measured_in": "a run building its shifts one at a time (no factor beside it), HIP events per factor",
@@ -545,8 +548,9 @@ def main():
             "launches_per_step": lu_launches // args.steps,
         },
         "roofline_apply": {
-            "kernel": "one application of M = U^-1 L^-1 P B (k_prepare_input; k_chunk_fwd, k_spike_chain x2, "
-                      "k_spike_fix, k_spike_correct; k_chunk_bwd, k_spike_chain x2, k_spike_fix, k_spike_correct)",
+            "kernel": "one application of M = U^-1 L^-1 P B (the sweeps of the blocks: k_chunk_fwd, k_block_states, "
+                      "k_spike_correct; k_chunk_bwd, k_block_states, k_spike_correct; then k_part_tips, "
+                      "k_part_correct; B v comes with the Arnoldi step)",
             "bound": "hbm",
             "achieved": apply_gbs,
             "peak": HBM_PEAK_GBS,
