@@ -60,7 +60,7 @@ int64_t part_block_len(int64_t n, int kl, int ku) {
         // down to max(256, 4 w) rows: a block is then a chunk or few of the sweeps and the LU
         // has bs / 16 panel steps (n = 14,167, k = 16: 50 blocks of 288 rows, an application
         // 114 us and a factor 4.3 ms against 199 us and 5.3 ms with 13 blocks of 1,104 in
-        // several chunks and chains).  Wider couplings take w / 16 panel steps per level of the
+        // several chunks and chains, both with the chunk sweeps of then; 76 us now).  Wider couplings take w / 16 panel steps per level of the
         // reduced inverse: blocks of at least max(1024, 4 w) rows.
         const int64_t rows = std::max<int64_t>(w <= kShortMaxW ? 256 : 1024, 4 * (int64_t)w);
         int64_t nb = std::min<int64_t>(1 + kReducedFill / w, n / rows);
@@ -245,7 +245,7 @@ __device__ bool gauss_jordan(cplx (&a)[16], int w, cplx (*colb)[kLdsMaxW], cplx*
 // Gauss-Jordan steps with partial pivoting over the unused rows, one row per thread.  vk[r] is
 // the step that row r was the pivot of (-1: none yet), plist[k] the pivot row of step k; at
 // the end row r holds row vk[r] of the inverse, column j its column plist[j].  Bound by the
-// 16 dependent column steps of a panel: 22 us a launch at w = 128, 32 us at w = 400, 0.2 and
+// 16 dependent column steps of a panel: 24 us a launch at w = 128, 34 us at w = 400, 0.2 and
 // 0.85 ms a level; inside one workgroup of 1,024 threads w = 128 took 0.49 ms.  (The band LU
 // of the reduced system with its column-by-column inverse did not reach w = 400: the
 // 200 x 200 grid's factor was one chain of 2,500 panel steps, 74 ms, and is now 11 blocks of

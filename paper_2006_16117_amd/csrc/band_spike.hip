@@ -1096,11 +1096,12 @@ int spike_max_nrhs(const SpikeFactor& f) {
 int64_t spike_chunk_len(int64_t n16, int kl, int K) {
     int64_t s = 0;
     if (const char* e = getenv("SIMM_SPIKE_CHUNK")) s = atoll(e);
-    // balance the chunk sweeps (~s/16 panel steps of ~2 us) against the two-level chain
+    // balance the chunk sweeps (~s/16 panel steps) against the two-level chain
     // (~L + G steps of ~5-12 us) and the per-shift unit-state responses, whose fixed cost
     // per chunk grows with P: s ~ (3/8) sqrt(100 n) (n = 40,000 step medians with the
     // multi-vector unit-state responses: s = 500, 750, 1000, 1250 -> ~675, ~663, ~683,
-    // ~700 ms)
+    // ~700 ms, measured with panel steps of ~2 us and this band factored whole.  A panel step
+    // now takes 0.6 and 0.45 us at kl = K = 16: longer chunks may pay, not measured)
     if (s <= 0) s = (int64_t)(std::sqrt((double)n16 * 100.0) * 0.375);
     // k_spike_correct stages the states of at most two chunks per 256-row block
     s = std::max<int64_t>(s, 256);

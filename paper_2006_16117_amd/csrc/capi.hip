@@ -82,10 +82,10 @@ struct JoinThreads {
 // Device blocks are kept for reuse while a pencil or shift is alive.  hipMalloc has to wait
 // for memory freed earlier to be wiped once a process has gone through the device's memory:
 // a run over a 200 x 200 grid (16 factors of 2 GB) took 460 ms and now and then 600 to
-// 3,600 ms, all of it in hipMalloc and hipMallocAsync; now 431 ms every time (one application
-// at n = 2,163 with its scratch 67 -> 49 us).  A block enters after a device-wide wait
-// (release_device; hipFree waits as well) or
-// a wait for the stream whose work used it (device_free_ordered), so any stream may take it.
+// 3,600 ms, all of it in hipMalloc and hipMallocAsync; 400 ms every time with blocks kept (one
+// application at n = 2,163 with its scratch 67 -> 48 us).  A block enters after a device-wide
+// wait (release_device; hipFree waits as well) or a wait for the stream whose work used it
+// (device_free_ordered), so any stream may take it.
 // (No events: they would be queried after their streams, which runs make and destroy, are
 // gone; and no device-wide wait for want of room while a run's threads are at work,
 // RunInFlight.)  Kept blocks are at most an eighth of the device's memory; those kept the
@@ -96,7 +96,8 @@ struct JoinThreads {
 // Batches (simm_run_batch) keep nothing: their threads (BatchThread) allocate from and free to
 // the runtime, scratch in the order of its stream, and make and destroy their streams.  A
 // batch of 64 pencils aborted on the host twice while its blocks and streams went through
-// the cache and the idle list below; the cause was not found, so batches are off both.
+// the cache and the idle list below; the cause was not found, so batches are off both (six
+// pencils of orders up to 6,000: 275 ms on them, 515 ms off them).
 //
 // Frees run in destructors: a block's entry is made when it is allocated and moves between the
 // tables as a node, so that no free allocates host memory or throws.

@@ -14,7 +14,7 @@
 // rows, then R Q_s + mu I and Q Q_s by the same rotations from the right, so that the
 // full upper triangular T results.
 //
-// A sweep is a serial chain of rotations (about 8,000 for m = 80 in all), so what counts
+// A sweep is a serial chain of rotations (about 9,400 for m = 80 in all), so what counts
 // is the latency of one, not arithmetic:
 //  * left phase, one wavefront, a lane per column: the row that the next rotation
 //    works on stays in registers, so a rotation's chain is a lane read of its leading
@@ -26,10 +26,10 @@
 //    applied from the right once the left phase is past rotation k + 1 (the rows it meets
 //    are then final), so these wavefronts follow the left phase two rotations behind, by a
 //    progress count in LDS, and a sweep takes little more than its left phase.
-// One matrix (a simm_shift_from_hessenberg call): m = 40 0.89 ms, m = 80 3.7 ms, m = 120 7.4 ms;
-// 2.3, 8.5 and 18.9 ms when every rotation went through LDS twice on one wavefront and a
-// second kernel replayed the rotations on Q.  About 670 cycles a rotation: 75 instructions of
-// the left phase, most of them FP64 and each waiting for the one before.
+// The kernel: m = 40 0.76 ms, m = 80 3.4 ms, m = 120 7.2 to 7.5 ms; 2.3, 8.5 and 18.9 ms (with
+// the call) when every rotation went through LDS twice on one wavefront and a second kernel
+// replayed the rotations on Q.  0.29 to 0.36 us a rotation: 75 instructions of the left phase,
+// most of them FP64 and each waiting for the one before.
 #include "common.hpp"
 #include "kernels.hpp"
 
