@@ -15,9 +15,10 @@
 //   e_m^T y = qlast . yhat  (residual, eq. (error)),  ||y|| = ||yhat||,
 //   s = Q (sum_j w_j yhat_j) / (2 pi i),
 // so the per-point work is one triangular solve.  Partial sums are combined across lanes
-// and wavefronts in a fixed order (bitwise reproducible).  Bound by the matrix and vector
-// FP64 instructions, about equal: 544 squares of 192 points,
-// m = 80: 190 us, a column at a time with one lane per row and lane reads 1,308 us.
+// and wavefronts in a fixed order (bitwise reproducible).  544 squares of 192 points, m = 80:
+// 184 us, a column at a time with one lane per row and lane reads 1,308 us.  Bound by the
+// dependent solves of one wavefront a SIMD (matrix cores 15 % busy, vector instructions about
+// 24 %) and by the last round of workgroups, an eighth full there.
 #include <algorithm>
 
 #include "common.hpp"
