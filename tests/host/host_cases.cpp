@@ -12,12 +12,13 @@
 #include <map>
 #include <new>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "fake_hip.hpp"
 #include "simm.h"
 
-static int failed = 0;
+static std::atomic<int> failed{0};
 #define CHECK(c)                                                                      \
     do {                                                                              \
         if (!(c)) {                                                                   \
@@ -351,6 +352,25 @@ static void helpers_free_nothing() {
     simm_pencil_destroy(p);
 }
 
+// Calls of several threads at once, a batch among them: all memory comes back.
+static void threads_side_by_side() {
+    std::vector<std::thread> threads;
+    for (int i = 0; i < 3; ++i)
+        threads.emplace_back([i]() {
+            for (int k = 0; k < 6; ++k) {
+                const int64_t n = 400 + 100 * i + 37 * k;
+                simm_pencil p = band(n, 8, 8);
+                CHECK(whole_use(p, ones(n)) == SIMM_OK);
+                simm_pencil_destroy(p);
+            }
+        });
+    for (int k = 0; k < 3; ++k) {
+        Batch b(4, k % 2 ? SIMM_FLAG_RELEASE_FACTORS : 0);
+        CHECK(b.run(2) == SIMM_OK);
+    }
+    for (auto& t : threads) t.join();
+}
+
 // Calls do their work where the system gives them no thread, or fewer than they ask for.
 static void no_threads() {
     for (long left : {0L, 1L, 3L, -1L}) {
@@ -407,6 +427,7 @@ int main(int argc, char** argv) {
         {"whole_factor_where_it_fits", whole_factor_where_it_fits},
         {"three_at_once", three_at_once},
         {"helpers_free_nothing", helpers_free_nothing},
+        {"threads_side_by_side", threads_side_by_side},
         {"no_threads", no_threads},
         {"no_host_memory", no_host_memory},
     };

@@ -30,7 +30,8 @@ def program(tmp_path_factory):
 @pytest.mark.parametrize("case", ["batch_keeps_nothing", "kept_while_a_quarter_is_free",
                                   "sizes_in_use_are_kept", "factors_ahead_fit",
                                   "blocks_have_the_size_asked_for", "spikes_with_less_scratch",
-                                  "whole_factor_where_it_fits", "three_at_once", "helpers_free_nothing", "no_threads", "no_host_memory"])
+                                  "whole_factor_where_it_fits", "three_at_once", "helpers_free_nothing",
+                                  "threads_side_by_side", "no_threads", "no_host_memory"])
 def test_host_case(program, case):
     out = subprocess.run([program, case], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
     assert out.returncode == 0, f"exit status {out.returncode}\n{out.stdout}"
