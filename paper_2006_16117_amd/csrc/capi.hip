@@ -97,7 +97,7 @@ struct JoinThreads {
 // the runtime, scratch in the order of its stream, and make and destroy their streams.  A
 // batch of 64 pencils aborted on the host twice while its blocks and streams went through
 // the cache and the idle list below; the cause was not found, so batches are off both (six
-// pencils of orders up to 6,000: 275 ms on them, 515 ms off them).
+// pencils of orders up to 6,000: 225 to 275 ms on them, 406 to 515 ms off them).
 //
 // Frees run in destructors: a block's entry is made when it is allocated and moves between the
 // tables as a node, so that no free allocates host memory or throws.
